@@ -84,6 +84,14 @@ __device__ __forceinline__ int wrap(long long c, int n) {
   return (int)(r < 0 ? r + n : r);
 }
 
+// floor(u) wrapped into the mesh.  Nodes inside the mesh, nearly all of them, need neither the 64-bit
+// conversion nor the 64-bit remainder, both of which are long instruction sequences (NaN takes the second
+// branch).
+__device__ __forceinline__ int wrap_floor(double u, int n) {
+  const double f = floor(u);
+  return f >= 0.0 && f < (double)n ? (int)f : wrap((long long)f, n);
+}
+
 // ---------------------------------------------------------------------------------------
 // Tile-sorted painting.  Particles are counting-sorted by the tile (TS^3 nodes) holding
 // their base node floor(u); each workgroup accumulates one tile plus the halo its window
@@ -108,18 +116,26 @@ constexpr int NCOPY = TILE_COUNT_COPIES;
 constexpr int RANK_BITS = 28;
 
 // Each thread takes CPT particles per round (blockDim apart) and issues their counter atomics
-// back to back, so CPT atomics per thread are in flight at once: the pass is bound by the
-// latency of returning atomics, not by their number.
+// back to back, so CPT atomics per thread are in flight at once: on a random catalog the pass is bound by
+// the latency of returning atomics, not by their number.  A catalog in some spatial order has runs of
+// particles of one tile, whose atomics on one counter would be done one after the other: the first lane of
+// such a run inside a wavefront counts for the whole run and the others take their ranks from it (one
+// particle on every node of a 128^3 mesh in mesh order: 511 us before, 24 now; 21 million random particles at
+// 512^3 0.85 to 0.90 ms either way).
 constexpr int CPT = 4;
 __global__ void k_tile_count(const double* __restrict__ pos, int64_t n, int64_t base, double o0, double o1,
-                             double o2, double scale, int nmesh, int ts, int ntiles, int* __restrict__ count,
+                             double o2, double scale, int nmesh, int ts_log2, int ntiles, int* __restrict__ count,
                              int* __restrict__ tile_of, int* __restrict__ rank) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x * CPT;
-  const int tpa = nmesh / ts;
+  const int tpa = nmesh >> ts_log2;
   const int copy = blockIdx.x % NCOPY;
+  const int lane = threadIdx.x & 63;
   int* cnt = count + (size_t)copy * (ntiles + 1);
-  for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x * CPT + threadIdx.x; i0 < n; i0 += stride) {
+  // (whole blocks stay in the loop: the lanes of a wavefront exchange their tiles)
+  for (int64_t b0 = (int64_t)blockIdx.x * blockDim.x * CPT; b0 < n; b0 += stride) {
+    const int64_t i0 = b0 + threadIdx.x;
     int tile[CPT], r[CPT];
+    unsigned long long heads[CPT];  // lanes at which a run begins
 #pragma unroll
     for (int j = 0; j < CPT; ++j) {
       const int64_t i = i0 + (int64_t)j * blockDim.x;
@@ -128,16 +144,30 @@ __global__ void k_tile_count(const double* __restrict__ pos, int64_t n, int64_t 
         double u[3];
         mesh_u(pos, i, o0, o1, o2, scale, u);
         int tc[3];
-        for (int a = 0; a < 3; ++a) tc[a] = wrap((long long)floor(u[a]), nmesh) / ts;
+        for (int a = 0; a < 3; ++a) tc[a] = wrap_floor(u[a], nmesh) >> ts_log2;
         tile[j] = (tc[0] * tpa + tc[1]) * tpa + tc[2];
       }
     }
 #pragma unroll
-    for (int j = 0; j < CPT; ++j)
-      if (tile[j] >= 0) r[j] = atomicAdd(&cnt[tile[j]], 1);
+    for (int j = 0; j < CPT; ++j) {
+      const int before = __shfl_up(tile[j], 1);  // (by every lane: an idle source would read as tile 0)
+      heads[j] = __ballot(lane == 0 || before != tile[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) {
+      r[j] = 0;
+      if ((heads[j] >> lane & 1) && tile[j] >= 0) {
+        const unsigned long long later = lane < 63 ? heads[j] >> (lane + 1) : 0;
+        r[j] = atomicAdd(&cnt[tile[j]], later ? __ffsll(later) : 64 - lane);
+      }
+    }
 #pragma unroll
     for (int j = 0; j < CPT; ++j) {
       const int64_t i = i0 + (int64_t)j * blockDim.x;
+      if (heads[j] != ~0ull) {  // (uniform)
+        const int first = 63 - __clzll(heads[j] & (~0ull >> (63 - lane)));
+        r[j] = __shfl(r[j], first) + lane - first;
+      }
       if (tile[j] >= 0) {
         tile_of[base + i] = tile[j];
         rank[base + i] = r[j] | (copy << RANK_BITS);
@@ -494,8 +524,8 @@ hipError_t launch_tile_sort(const double* pos, int64_t n, int64_t base, const do
   int64_t blocks = (n + 256 * CPT - 1) / (256 * CPT);
   if (blocks > 16384) blocks = 16384;
   const int tpa = nmesh / ts;
-  k_tile_count<<<(unsigned)blocks, 256, 0, s>>>(pos, n, base, origin[0], origin[1], origin[2], scale, nmesh, ts,
-                                                tpa * tpa * tpa, count, tile_of, rank);
+  k_tile_count<<<(unsigned)blocks, 256, 0, s>>>(pos, n, base, origin[0], origin[1], origin[2], scale, nmesh,
+                                                __builtin_ctz(ts), tpa * tpa * tpa, count, tile_of, rank);
   return hipGetLastError();
 }
 
