@@ -97,7 +97,7 @@ __device__ __forceinline__ int wrap_floor(double u, int n) {
 // their base node floor(u); each workgroup accumulates one tile plus the halo its window
 // reaches, one LDS region per mesh (for TSC (TS + 3)^3 nodes from t0 - 1 on the plain mesh and
 // (TS + 2)^3 from t0 on the +1/2 interlaced one; PaintReach), then adds the non-zero region
-// cells to the global meshes with atomics.  A tap that falls outside its region (only possible
+// cells to the global meshes with atomics (a block may take several tiles of a row at once).  A tap that falls outside its region (only possible
 // through FP64 rounding at a cell face) goes straight to a global atomic.
 // ---------------------------------------------------------------------------------------
 __device__ __forceinline__ void mesh_u(const double* __restrict__ pos, int64_t i, double o0, double o1, double o2,
@@ -271,83 +271,92 @@ __global__ void k_tile_scatter(const int* __restrict__ tile_of, const int* __res
   }
 }
 
-// Unwrapped taps of the window at u: nodes c0 + j (j < W) with weights wt[j].
-template <int W>
-__device__ __forceinline__ void taps_unwrapped(double u, long long* c0, double* wt) {
+// Taps of the window at u: nodes c + TAP0 + j (j < W) with weights wt[j], where c is the integer returned.
+template <int W> constexpr int TAP0 = W == 3 ? -1 : 0;
+template <int W> __device__ __forceinline__ double taps(double u, double* wt) {
   if constexpr (W == 1) {
-    *c0 = (long long)floor(__dadd_rn(u, 0.5));
     wt[0] = 1.0;
+    return floor(__dadd_rn(u, 0.5));
   } else if constexpr (W == 2) {
     const double c = floor(u);
     const double d = __dsub_rn(u, c);
-    *c0 = (long long)c;
     wt[0] = 1.0 - d;
     wt[1] = d;
+    return c;
   } else {
     const double c = floor(__dadd_rn(u, 0.5));
     const double d = __dsub_rn(u, c);
-    *c0 = (long long)c - 1;
     const double a = 0.5 - d, b = 0.5 + d;
     wt[0] = 0.5 * a * a;
     wt[1] = 0.75 - d * d;
     wt[2] = 0.5 * b * b;
+    return c;
   }
 }
 
-// One tap into the LDS region: FP64 atomic add (FP64 meshes), or, for FP32 meshes, an
-// integer add of the tap rounded to a multiple of 1/sc (fixed point; 64-bit integer LDS atomics
-// are faster than FP64 ones on gfx950, and FP32 LDS atomics far slower).
+// One tap, a times b (the scale sc inside), into the LDS region: FP64 atomic add (FP64 meshes; sc = 1),
+// or, for FP32 meshes, an integer add of the tap rounded to a multiple of 1/sc (fixed point; 64-bit integer
+// LDS atomics are faster than FP64 ones on gfx950, and FP32 LDS atomics far slower).
 // Deterministic mode (FIXED for FP64 too): every tap is rounded to a multiple of 1/sc of one
 // scale shared by all tiles, so integer sums of the taps are exact in any order.
-template <typename T, bool DET>
-__device__ __forceinline__ void region_add(double* __restrict__ reg, int i, double v, double sc) {
-  if constexpr (sizeof(T) == 4 || DET)
-    lds_atomic_add<unsigned long long>(reinterpret_cast<unsigned long long*>(reg) + i,
-                                       (unsigned long long)__double2ll_rn(v * sc));
-  else
-    lds_atomic_add<double>(reg + i, v);
+// The pass is bound by vector instructions, a third of which were the conversion to 64 bits, so a b is
+// split by two fused adds instead: adding 3 2^83 rounds it to a multiple of 2^32 whose quotient is the low
+// word of the sum, and adding 3 2^51 to the rest, |rest| <= 2^31, leaves that as a 64-bit integer above the
+// constant's own bits.  For |a b| <= 2^61 (callers leave out NaN and infinities).
+__device__ __forceinline__ long long fixed_product(double a, double b) {
+  constexpr double HI = 0x1.8p84, LO = 0x1.8p52;
+  const double h = fma(a, b, HI);
+  const double l = fma(a, b, -(h - HI)) + LO;
+  const unsigned long long hb = __double_as_longlong(h), lb = __double_as_longlong(l);
+  return (long long)(lb + (hb << 32) - 0x4338000000000000ull);
 }
 
+template <typename T, bool DET>
+__device__ __forceinline__ void region_add(double* __restrict__ reg, int i, double a, double b) {
+  if constexpr (sizeof(T) == 4 || DET)
+    lds_atomic_add<unsigned long long>(reinterpret_cast<unsigned long long*>(reg) + i,
+                                       (unsigned long long)fixed_product(a, b));
+  else
+    lds_atomic_add<double>(reg + i, a * b);
+}
+
+// Slabs a0 <= a < a1 (tap index along x) of one particle's taps, wsc = weight times sc, into the
+// region of sides rsz, rsz, rz.  c: what taps() gave per axis, wt: its weights, rel: the first tap's node in the region.
 template <typename T, int W, bool DET>
-__device__ __forceinline__ void tile_scatter(double* __restrict__ reg, T* __restrict__ mesh,
-                                             unsigned long long* __restrict__ acc, const double* u, double wgt,
-                                             int nmesh, const long long* r0, int rsz, double sc) {
-  long long c0[3];
-  double w[3][W];
-  taps_unwrapped<W>(u[0], &c0[0], w[0]);
-  taps_unwrapped<W>(u[1], &c0[1], w[1]);
-  taps_unwrapped<W>(u[2], &c0[2], w[2]);
-  const int ra0 = (int)(c0[0] - r0[0]), rb0 = (int)(c0[1] - r0[1]), rc0 = (int)(c0[2] - r0[2]);
-  const bool inside = ra0 >= 0 && ra0 + W <= rsz && rb0 >= 0 && rb0 + W <= rsz && rc0 >= 0 && rc0 + W <= rsz;
-  if (inside) {
+__device__ __forceinline__ void scatter_slabs(double* __restrict__ reg, T* __restrict__ mesh,
+                                              unsigned long long* __restrict__ acc, const double* c,
+                                              const double (*wt)[W], double wsc, int nmesh, const int* rel, int rsz,
+                                              int rz, double isc, int a0, int a1) {
+  const bool inside = rel[0] >= 0 && rel[0] + W <= rsz && rel[1] >= 0 && rel[1] + W <= rsz && rel[2] >= 0 &&
+                      rel[2] + W <= rz;
+  for (int a = a0; a < a1; ++a) {
+    double w0 = wt[0][0];
 #pragma unroll
-    for (int a = 0; a < W; ++a) {
-      const double wa = wgt * w[0][a];
+    for (int j = 1; j < W; ++j) w0 = a == j ? wt[0][j] : w0;
+    const double wa = wsc * w0;
+    if (inside) {
+      const int row = ((rel[0] + a) * rsz + rel[1]) * rz + rel[2];
 #pragma unroll
       for (int b = 0; b < W; ++b) {
-        const double wab = wa * w[1][b];
-        const int row = ((ra0 + a) * rsz + (rb0 + b)) * rsz + rc0;
+        const double wab = wa * wt[1][b];
 #pragma unroll
-        for (int c = 0; c < W; ++c) region_add<T, DET>(reg, row + c, wab * w[2][c], sc);
+        for (int d = 0; d < W; ++d) region_add<T, DET>(reg, row + b * rz + d, wab, wt[2][d]);
       }
+      continue;
     }
-    return;
-  }
-  // a tap outside the LDS region (FP64 rounding at a cell face): straight to the mesh
-#pragma unroll
-  for (int a = 0; a < W; ++a) {
-    const double wa = wgt * w[0][a];
+    // a tap outside the LDS region (FP64 rounding at a cell face): straight to the mesh
+    const long long g0 = (long long)c[0] + TAP0<W> + a;
 #pragma unroll
     for (int b = 0; b < W; ++b) {
-      const double wab = wa * w[1][b];
+      const double wab = wa * wt[1][b];
 #pragma unroll
-      for (int c = 0; c < W; ++c) {
-        const size_t g = ((size_t)wrap(c0[0] + a, nmesh) * nmesh + wrap(c0[1] + b, nmesh)) * nmesh +
-                         wrap(c0[2] + c, nmesh);
+      for (int d = 0; d < W; ++d) {
+        const size_t g = ((size_t)wrap(g0, nmesh) * nmesh + wrap((long long)c[1] + TAP0<W> + b, nmesh)) * nmesh +
+                         wrap((long long)c[2] + TAP0<W> + d, nmesh);
         if constexpr (DET)
-          atomicAdd(&acc[g], (unsigned long long)__double2ll_rn(wab * w[2][c] * sc));
+          atomicAdd(&acc[g], (unsigned long long)fixed_product(wab, wt[2][d]));
         else
-          unsafeAtomicAdd(&mesh[g], (T)(wab * w[2][c]));
+          unsafeAtomicAdd(&mesh[g], (T)(wab * wt[2][d] * isc));
       }
     }
   }
@@ -360,108 +369,151 @@ __device__ __forceinline__ void tile_scatter(double* __restrict__ reg, T* __rest
 // {b, b + 1} (plain) and b + 1 (interlaced).  CIC: b, b + 1 (plain) and floor(u + 1/2) + {0, 1}
 // within b .. b + 2.  TSC: floor(u + 1/2) + {-1, 0, 1} within b - 1 .. b + 2 (plain) and
 // b + 1 + {-1, 0, 1} (interlaced).  A tap that FP64 rounding of u + 1/2 at a cell face moves
-// outside goes to the mesh directly (tile_scatter).
+// outside goes to the mesh directly (scatter_slabs).
 template <int W> struct PaintReach;
 template <> struct PaintReach<1> { static constexpr int LO1 = 0, EXT1 = 1, LO2 = 1, EXT2 = 0; };
 template <> struct PaintReach<2> { static constexpr int LO1 = 0, EXT1 = 1, LO2 = 0, EXT2 = 2; };
 template <> struct PaintReach<3> { static constexpr int LO1 = -1, EXT1 = 3, LO2 = 0, EXT2 = 2; };
 
-// Add the non-zero cells of one LDS region (side N, origin t0 + LO) to the mesh with global
-// atomics (or, DET, the integer sums to the 64-bit accumulators).
-template <typename T, bool DET, int N, int LO>
-__device__ __forceinline__ void flush_region(const double* __restrict__ reg, T* __restrict__ mesh,
+// Add the non-zero cells of one column along x (NX cells, (y, z) cell k of the region of z side NZ) to the
+// mesh with global atomics (DET: the integer sums to the 64-bit accumulators).  Region node i of an axis is
+// mesh node t0 + LO + i, wrapped once at most.
+template <typename T, bool DET, int NX, int NZ, int LO>
+__device__ __forceinline__ void flush_column(const double* __restrict__ reg, int k, T* __restrict__ mesh,
                                              unsigned long long* __restrict__ acc, const int* t0, int nmesh,
                                              double isc) {
-  for (int i = threadIdx.x; i < N * N * N; i += blockDim.x) {
-    const long long q = reinterpret_cast<const long long*>(reg)[i];
-    T v;
-    if constexpr (sizeof(T) == 4 && !DET)
-      v = (T)((double)q * isc);
-    else
-      v = (T)reg[i];
-    if (DET ? q == 0 : v == T(0)) continue;
-    // region node (ra, rb, rc) is mesh node t0 + LO + (ra, rb, rc), wrapped once at most
-    const int rc = i % N, rb = (i / N) % N, ra = i / (N * N);
-    int gx = t0[0] + LO + ra, gy = t0[1] + LO + rb, gz = t0[2] + LO + rc;
-    gx += gx < 0 ? nmesh : (gx >= nmesh ? -nmesh : 0);
-    gy += gy < 0 ? nmesh : (gy >= nmesh ? -nmesh : 0);
-    gz += gz < 0 ? nmesh : (gz >= nmesh ? -nmesh : 0);
-    const size_t g = ((size_t)gx * nmesh + gy) * nmesh + gz;
-    if constexpr (DET)
-      atomicAdd(&acc[g], (unsigned long long)q);
-    else
-      unsafeAtomicAdd(&mesh[g], v);
+  const int rb = k / NZ, rc = k - rb * NZ;
+  int gx = t0[0] + LO, gy = t0[1] + LO + rb, gz = t0[2] + LO + rc;
+  gx += gx < 0 ? nmesh : (gx >= nmesh ? -nmesh : 0);
+  gy += gy < 0 ? nmesh : (gy >= nmesh ? -nmesh : 0);
+  gz += gz < 0 ? nmesh : (gz >= nmesh ? -nmesh : 0);
+  const size_t plane = (size_t)nmesh * nmesh, cell = (size_t)gy * nmesh + gz;
+  constexpr int CH = 11;  // cells read at once
+#pragma unroll 1
+  for (int i0 = 0; i0 < NX; i0 += CH) {
+    long long q[CH];
+#pragma unroll
+    for (int i = 0; i < CH; ++i)
+      q[i] = i0 + i < NX ? reinterpret_cast<const long long*>(reg)[(i0 + i) * (NX * NZ) + k] : 0;
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+      // (as bits: a region holds no -0.0, and a tap that underflows to 0 adds nothing)
+      if (q[i] != 0) {
+        if constexpr (DET)
+          atomicAdd(&acc[gx * plane + cell], (unsigned long long)q[i]);
+        else if constexpr (sizeof(T) == 4)
+          unsafeAtomicAdd(&mesh[gx * plane + cell], (T)((double)q[i] * isc));
+        else
+          unsafeAtomicAdd(&mesh[gx * plane + cell], (T)__longlong_as_double(q[i]));
+      }
+      if (++gx == nmesh) gx = 0;
+    }
   }
 }
 
+// A painting block takes ZT consecutive tiles of a row along z, whose particles are consecutive too.
+template <int W, int TS, int ZT> struct PaintShape {
+  using R = PaintReach<W>;
+  static constexpr int N1 = TS + R::EXT1, N2 = TS + R::EXT2, Z1 = TS * ZT + R::EXT1, Z2 = TS * ZT + R::EXT2;
+  static constexpr int CELLS1 = N1 * N1 * Z1, CELLS2 = N2 * N2 * Z2;
+  static constexpr int THREADS = ZT == 4 ? 512 : 256;
+};
+
 // DET: the tiles' integer sums go to the 64-bit accumulators acc1 / acc2 (one per mesh) with
 // integer atomics at the shared scale *gsc, instead of floating-point atomics to d1 / d2.
-template <typename T, int W, int TS, bool DET>
-__global__ void __launch_bounds__(256) k_paint_tiles(const int* __restrict__ off, const double4* __restrict__ payload,
-                                                     double o0, double o1, double o2, double scale, int nmesh,
-                                                     T* __restrict__ d1, T* __restrict__ d2,
-                                                     const double* __restrict__ wmax_d,
-                                                     const double* __restrict__ wmax_r, double alpha,
-                                                     unsigned long long* __restrict__ acc1,
-                                                     unsigned long long* __restrict__ acc2,
-                                                     const double* __restrict__ gsc) {
+template <typename T, int W, int TS, int ZT, bool DET>
+__global__ void __launch_bounds__((PaintShape<W, TS, ZT>::THREADS))
+    k_paint_tiles(const int* __restrict__ off, const double4* __restrict__ payload, double o0, double o1, double o2,
+                  double scale, int nmesh, T* __restrict__ d1, T* __restrict__ d2, const double* __restrict__ wmax_d,
+                  const double* __restrict__ wmax_r, double alpha, unsigned long long* __restrict__ acc1,
+                  unsigned long long* __restrict__ acc2, const double* __restrict__ gsc) {
   constexpr int ts = TS;
   using R = PaintReach<W>;
-  constexpr int n1 = ts + R::EXT1, n2 = ts + R::EXT2;  // region sides of the two meshes
+  using S = PaintShape<W, TS, ZT>;
+  constexpr int n1 = S::N1, n2 = S::N2, z1 = S::Z1, z2 = S::Z2;  // region sides of the two meshes
   extern __shared__ __align__(16) unsigned char smem[];
-  // natural tile order: consecutive tiles land on different XCDs, which spreads the dense
-  // survey region evenly (measured faster than XCD-local orders that keep halos in one L2)
-  const int tile = blockIdx.x;
-  const int start = off[tile], end = off[tile + 1];
+  const int tpa = nmesh / ts;
+  // Consecutive blocks go to consecutive XCDs.  The start of a row of tiles moves on by one from row to row:
+  // in the tiles' own order an XCD would take every 8th block of every row, which for rows of 8 or 16 blocks
+  // is a fixed range of z, and a survey that fills part of the box loads some XCDs twice as much as others.
+  const int row = blockIdx.x / (tpa / ZT);
+  const int tile = (row * (tpa / ZT) + (blockIdx.x + row) % (tpa / ZT)) * ZT;
+  int at[ZT + 1];
+#pragma unroll
+  for (int k = 0; k <= ZT; ++k) at[k] = off[tile + k];
+  const int start = at[0], end = at[ZT];
   if (start == end) return;
   double* r1 = reinterpret_cast<double*>(smem);   // FP64 accumulation for both precisions
-  double* r2 = r1 + n1 * n1 * n1;
   const bool two = d2 != nullptr;
-  const int ncells = n1 * n1 * n1 + (two ? n2 * n2 * n2 : 0);
-  for (int i = threadIdx.x; i < ncells; i += blockDim.x) r1[i] = 0.0;
-  const int tpa = nmesh / ts;
+  const int ncells = S::CELLS1 + (two ? S::CELLS2 : 0);
+  for (int i = threadIdx.x; i < (ncells + 1) / 2; i += blockDim.x)
+    reinterpret_cast<double2*>(smem)[i] = make_double2(0.0, 0.0);
   const int tz = tile % tpa, ty = (tile / tpa) % tpa, tx = tile / (tpa * tpa);
   const int t0[3] = {tx * ts, ty * ts, tz * ts};
-  // fixed-point scale (FP32 meshes): no region cell can exceed B = (particles of the tile) x
-  // (largest |payload weight|), since a particle's taps sum to its weight; B sc <= 2^61
+  // fixed-point scale (FP32 meshes): no region cell can exceed B = (particles that reach it: those of
+  // two neighbouring tiles of the row) x (largest |payload weight|), since a particle's taps sum to its
+  // weight; B sc <= 2^61
   double sc = 1.0;
   if constexpr (DET) {
     sc = *gsc;
   } else if constexpr (sizeof(T) == 4) {
+    int most = at[1] - at[0];
+#pragma unroll
+    for (int k = 2; k <= ZT; ++k) most = max(most, at[k] - at[k - 2]);
     const double wm = fmax(*wmax_d, wmax_r ? alpha * *wmax_r : 0.0);
-    const double bound = (double)(end - start) * wm;
+    const double bound = (double)most * wm;
     int e = 0;
     if (bound > 0.0) (void)frexp(bound, &e);  // bound < 2^e
     sc = ldexp(1.0, 61 - e);
   }
+  const double isc = 1.0 / sc;  // a power of two: exact
   __syncthreads();
-  for (int j = start + threadIdx.x; j < end; j += blockDim.x) {
-    const double4 p = payload[j];
-    const double wgt = p.w;
+  // A unit of work is one particle on one mesh, or, where that leaves most of the block idle, one slab of
+  // its taps (slabs everywhere repeat the weights and cost a dense survey 1.07 -> 1.68 ms).
+  const bool fine = (end - start) < (int)blockDim.x / 2;
+  const int per = (two ? 2 : 1) * (fine ? W : 1);
+  const int units = (end - start) * per;
+  for (int j = threadIdx.x; j < units; j += blockDim.x) {
+    const int q = fine ? (two ? j / (2 * W) : j / W) : (two ? j / 2 : j);
+    const int sub = j - q * per;
+    const bool second = fine ? sub >= W : sub == 1;
+    const int a0 = fine ? (second ? sub - W : sub) : 0;
+    const double4 p = payload[start + q];
     double u[3];
     u[0] = __dmul_rn(__dsub_rn(p.x, o0), scale);
     u[1] = __dmul_rn(__dsub_rn(p.y, o1), scale);
     u[2] = __dmul_rn(__dsub_rn(p.z, o2), scale);
-    // region origins (unwrapped, in this particle's frame): the tile origin t0 plus LO
-    long long r01[3], r02[3];
+    double c[3], wt[3][W];
+    int rel[3];
+    const double wsc = p.w * sc;
+    if constexpr (sizeof(T) == 4 || DET) {  // (taps that are not numbers count as nothing)
+      if (!(fabs(wsc) <= 0x1p62)) continue;
+      if (W > 1 && !(fabs(u[0]) + fabs(u[1]) + fabs(u[2]) < __builtin_huge_val())) continue;
+    }
     for (int a = 0; a < 3; ++a) {
-      const long long cu = (long long)floor(u[a]);
-      const long long base = cu - (wrap(cu, nmesh) - t0[a]);
-      r01[a] = base + R::LO1;
-      r02[a] = base + R::LO2;
+      const int lo = second ? R::LO2 : R::LO1;
+      c[a] = taps<W>(second ? __dadd_rn(u[a], 0.5) : u[a], wt[a]);
+      // the region begins at the tile origin t0 plus LO in the particle's frame, which is the mesh's own for
+      // base nodes inside the mesh
+      const double f = floor(u[a]);
+      if (f >= 0.0 && f < (double)nmesh) {
+        rel[a] = (int)(c[a] - (double)(t0[a] + lo - TAP0<W>));
+      } else {
+        const long long cu = (long long)f;
+        rel[a] = (int)((long long)c[a] + TAP0<W> - (cu - (wrap(cu, nmesh) - t0[a]) + lo));
+      }
     }
-    tile_scatter<T, W, DET>(r1, d1, acc1, u, wgt, nmesh, r01, n1, sc);
-    if (two) {
-      u[0] = __dadd_rn(u[0], 0.5);
-      u[1] = __dadd_rn(u[1], 0.5);
-      u[2] = __dadd_rn(u[2], 0.5);
-      tile_scatter<T, W, DET>(r2, d2, acc2, u, wgt, nmesh, r02, n2, sc);
-    }
+    scatter_slabs<T, W, DET>(second ? r1 + S::CELLS1 : r1, second ? d2 : d1, second ? acc2 : acc1, c, wt,
+                             wsc, nmesh, rel, second ? n2 : n1, second ? z2 : z1, isc, a0,
+                             fine ? a0 + 1 : W);
   }
   __syncthreads();
-  const double isc = 1.0 / sc;  // a power of two: exact
-  flush_region<T, DET, n1, R::LO1>(r1, d1, acc1, t0, nmesh, isc);
-  if (two) flush_region<T, DET, n2, R::LO2>(r2, d2, acc2, t0, nmesh, isc);
+  for (int j = threadIdx.x; j < n1 * z1 + (two ? n2 * z2 : 0); j += blockDim.x) {
+    if (j < n1 * z1)
+      flush_column<T, DET, n1, z1, R::LO1>(r1, j, d1, acc1, t0, nmesh, isc);
+    else
+      flush_column<T, DET, n2, z2, R::LO2>(r1 + S::CELLS1, j - n1 * z1, d2, acc2, t0, nmesh, isc);
+  }
 }
 
 // Deterministic mode: the shared fixed-point scale.  A node's value is a sum of taps of the
@@ -551,12 +603,6 @@ hipError_t launch_paint_tiles(const int* off, const void* payload, int ntiles, c
                               const double* wmax_r, double alpha, hipStream_t s, unsigned long long* acc,
                               double* gsc) {
   const bool two = d2 != nullptr;
-  int e1 = 0, e2 = 0;  // region sides ts + e1 (plain mesh) and ts + e2 (interlaced mesh)
-  if (window == 1) { e1 = PaintReach<1>::EXT1; e2 = PaintReach<1>::EXT2; }
-  else if (window == 2) { e1 = PaintReach<2>::EXT1; e2 = PaintReach<2>::EXT2; }
-  else { e1 = PaintReach<3>::EXT1; e2 = PaintReach<3>::EXT2; }
-  const size_t c1 = (size_t)(ts + e1) * (ts + e1) * (ts + e1), c2 = (size_t)(ts + e2) * (ts + e2) * (ts + e2);
-  const size_t sm = sizeof(double) * (c1 + (two ? c2 : 0));
   const double4* pl = (const double4*)payload;
   unsigned long long* acc2 = (acc && two) ? acc + (size_t)nmesh * nmesh * nmesh : nullptr;
   if (acc) {
@@ -564,21 +610,29 @@ hipError_t launch_paint_tiles(const int* off, const void* payload, int ntiles, c
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-#define PKM_PAINT(WV, TV)                                                                                      \
-  if (window == WV && ts == TV) {                                                                              \
+  const int tpa = nmesh / ts;
+#define PKM_PAINT(WV, TV, ZV)                                                                                  \
+  if (window == WV && ts == TV && tpa % ZV == 0) {                                                             \
+    using S = PaintShape<WV, TV, ZV>;                                                                          \
+    const size_t sm = sizeof(double) * ((S::CELLS1 + (two ? S::CELLS2 : 0) + 1) & ~1);                         \
     if (acc)                                                                                                   \
-      k_paint_tiles<T, WV, TV, true><<<ntiles, 256, sm, s>>>(off, pl, origin[0], origin[1], origin[2], scale,  \
-                                                             nmesh, d1, d2, wmax_d, wmax_r, alpha, acc, acc2,  \
-                                                             gsc);                                            \
+      k_paint_tiles<T, WV, TV, ZV, true><<<ntiles / ZV, S::THREADS, sm, s>>>(                                  \
+          off, pl, origin[0], origin[1], origin[2], scale, nmesh, d1, d2, wmax_d, wmax_r, alpha, acc, acc2, gsc); \
     else                                                                                                       \
-      k_paint_tiles<T, WV, TV, false><<<ntiles, 256, sm, s>>>(off, pl, origin[0], origin[1], origin[2], scale, \
-                                                              nmesh, d1, d2, wmax_d, wmax_r, alpha, nullptr,   \
-                                                              nullptr, nullptr);                              \
+      k_paint_tiles<T, WV, TV, ZV, false><<<ntiles / ZV, S::THREADS, sm, s>>>(                                 \
+          off, pl, origin[0], origin[1], origin[2], scale, nmesh, d1, d2, wmax_d, wmax_r, alpha, nullptr, nullptr, \
+          nullptr);                                                                                            \
     return hipGetLastError();                                                                                  \
   }
-  PKM_PAINT(1, 4) PKM_PAINT(2, 4) PKM_PAINT(3, 4)
-  PKM_PAINT(1, 8) PKM_PAINT(2, 8) PKM_PAINT(3, 8)
-  PKM_PAINT(1, 16) PKM_PAINT(2, 16) PKM_PAINT(3, 16)
+  // Tiles per block (8-node tiles).  More of them mean fewer halo cells and fewer, longer rows of atomics,
+  // which the memory side takes at about 20 a nanosecond whatever their length (512^3, 2 million uniform
+  // particles: 1.30, 1.10, 1.01 ms for 1, 2, 4); fewer mean more blocks to spread a survey's dense part over
+  // (128^3 mock 52, 71, 66 us; 256^3 survey 213, 175, 240 us; 512^3 0.80, 0.82, 0.76 ms).
+  if (ntiles >= 1 << 18) { PKM_PAINT(1, 8, 4) PKM_PAINT(2, 8, 4) PKM_PAINT(3, 8, 4) }
+  if (ntiles >= 1 << 15) { PKM_PAINT(1, 8, 2) PKM_PAINT(2, 8, 2) PKM_PAINT(3, 8, 2) }
+  PKM_PAINT(1, 8, 1) PKM_PAINT(2, 8, 1) PKM_PAINT(3, 8, 1)
+  PKM_PAINT(1, 4, 1) PKM_PAINT(2, 4, 1) PKM_PAINT(3, 4, 1)
+  PKM_PAINT(1, 16, 1) PKM_PAINT(2, 16, 1) PKM_PAINT(3, 16, 1)
 #undef PKM_PAINT
   return hipErrorInvalidValue;
 }
