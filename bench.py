@@ -54,7 +54,9 @@ def stage_bytes(nmesh: int, es: int, n_part: int, nfields: int) -> dict:
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 # Sources whose change invalidates stored HBM counter readings of the transform kernels.
-TRAFFIC_SOURCES = ["paper_1704_02357_amd/csrc/kernels_fft.hip", "paper_1704_02357_amd/csrc/device_common.hpp",
+TRAFFIC_SOURCES = ["paper_1704_02357_amd/csrc/kernels_fft.hip", "paper_1704_02357_amd/csrc/columns.hpp",
+                   "paper_1704_02357_amd/csrc/fields_pre.hpp", "paper_1704_02357_amd/csrc/fields_post.hpp",
+                   "paper_1704_02357_amd/csrc/fft_common.hpp", "paper_1704_02357_amd/csrc/device_common.hpp",
                    "paper_1704_02357_amd/csrc/kernels.hpp", "paper_1704_02357_amd/csrc/plan.hip"]
 
 

@@ -17,7 +17,9 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libpkm.so")
 
-SOURCES = ["kernels_paint.hip", "kernels_fft.hip", "plan.hip", "runtime.hip", "host_math.cpp"]
+KERNEL_SOURCES = ["kernels_post_f32.hip", "kernels_post_f64.hip", "kernels_pre_f32.hip", "kernels_pre_f64.hip",
+                  "kernels_col_f32.hip", "kernels_col_f64.hip", "kernels_fft.hip", "kernels_paint.hip"]
+SOURCES = KERNEL_SOURCES + ["plan.hip", "runtime.hip", "host_math.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function", "-Wno-unused-result",
@@ -105,7 +107,7 @@ def build_sanitized(verbose: bool = False) -> str:
     failed = [(src, out) for (src, out), (_, p) in zip(failed, procs) if p.returncode != 0]
     if failed:
         raise RuntimeError("sanitized compile failed:\n" + "\n".join(f"--- {s}\n{o}" for s, o in failed))
-    kernels = [os.path.join(BUILD, s) for s in ("kernels_paint.o", "kernels_fft.o")]
+    kernels = [os.path.join(BUILD, os.path.splitext(s)[0] + ".o") for s in KERNEL_SOURCES]
     for k in kernels:
         if not os.path.exists(k):
             raise RuntimeError(f"{k} missing: run build() first")

@@ -28,7 +28,7 @@ template <typename T, bool INV> __device__ __forceinline__ cx<T> rot_mi(cx<T> a)
 }
 
 // ---------------------------------------------------------------------------------------
-// Radix-R DFT on registers: y_s = sum_t x_t exp(-+2 pi i s t / R), R in {2,3,4,6,8}.
+// Radix-R DFT on registers: y_s = sum_t x_t exp(-+2 pi i s t / R), R in {2,3,4,6,8,12,16}.
 // ---------------------------------------------------------------------------------------
 template <typename T, bool INV> __device__ __forceinline__ void dft2(cx<T>* v) {
   cx<T> a = v[0], b = v[1];
@@ -95,12 +95,77 @@ template <typename T, bool INV> __device__ __forceinline__ void dft8(cx<T>* v) {
   v[1] = b[0]; v[3] = b[1]; v[5] = b[2]; v[7] = b[3];
 }
 
+// a * exp(-+2 pi i j / D) for the constant (cos, sin) of that angle.
+template <typename T, bool INV> __device__ __forceinline__ cx<T> rot_c(cx<T> a, double c, double s) {
+  const T cc = (T)c, ss = INV ? (T)s : (T)(-s);
+  return mk<T>(a.x * cc - a.y * ss, a.x * ss + a.y * cc);
+}
+
+// 12 = 4 x 3: t = t0 + 4 t1, s = s1 + 3 s0; DFTs of 3 over t1, twiddles W12^(t0 s1), DFTs of 4.
+template <typename T, bool INV> __device__ __forceinline__ void dft12(cx<T>* v) {
+  const double h = 0.86602540378443864676;
+  cx<T> a[4][3];
+#pragma unroll
+  for (int t0 = 0; t0 < 4; ++t0) {
+#pragma unroll
+    for (int t1 = 0; t1 < 3; ++t1) a[t0][t1] = v[t0 + 4 * t1];
+    dft3<T, INV>(a[t0]);
+  }
+  a[1][1] = rot_c<T, INV>(a[1][1], h, 0.5);      // W12^1
+  a[1][2] = rot_c<T, INV>(a[1][2], 0.5, h);      // W12^2
+  a[2][1] = rot_c<T, INV>(a[2][1], 0.5, h);      // W12^2
+  a[2][2] = rot_c<T, INV>(a[2][2], -0.5, h);     // W12^4
+  a[3][1] = rot_mi<T, INV>(a[3][1]);             // W12^3
+  a[3][2] = mk<T>(-a[3][2].x, -a[3][2].y);       // W12^6
+#pragma unroll
+  for (int s1 = 0; s1 < 3; ++s1) {
+    cx<T> b[4];
+#pragma unroll
+    for (int t0 = 0; t0 < 4; ++t0) b[t0] = a[t0][s1];
+    dft4<T, INV>(b);
+#pragma unroll
+    for (int s0 = 0; s0 < 4; ++s0) v[s1 + 3 * s0] = b[s0];
+  }
+}
+
+// 16 = 4 x 4: t = t0 + 4 t1, s = s1 + 4 s0; DFTs of 4 over t1, twiddles W16^(t0 s1), DFTs of 4.
+template <typename T, bool INV> __device__ __forceinline__ void dft16(cx<T>* v) {
+  const double r = 0.70710678118654752440, c1 = 0.92387953251128675613, c3 = 0.38268343236508977173;
+  cx<T> a[4][4];
+#pragma unroll
+  for (int t0 = 0; t0 < 4; ++t0) {
+#pragma unroll
+    for (int t1 = 0; t1 < 4; ++t1) a[t0][t1] = v[t0 + 4 * t1];
+    dft4<T, INV>(a[t0]);
+  }
+  a[1][1] = rot_c<T, INV>(a[1][1], c1, c3);      // W16^1
+  a[1][2] = rot_c<T, INV>(a[1][2], r, r);        // W16^2
+  a[1][3] = rot_c<T, INV>(a[1][3], c3, c1);      // W16^3
+  a[2][1] = rot_c<T, INV>(a[2][1], r, r);        // W16^2
+  a[2][2] = rot_mi<T, INV>(a[2][2]);             // W16^4
+  a[2][3] = rot_c<T, INV>(a[2][3], -r, r);       // W16^6
+  a[3][1] = rot_c<T, INV>(a[3][1], c3, c1);      // W16^3
+  a[3][2] = rot_c<T, INV>(a[3][2], -r, r);       // W16^6
+  a[3][3] = rot_c<T, INV>(a[3][3], -c1, -c3);    // W16^9
+#pragma unroll
+  for (int s1 = 0; s1 < 4; ++s1) {
+    cx<T> b[4];
+#pragma unroll
+    for (int t0 = 0; t0 < 4; ++t0) b[t0] = a[t0][s1];
+    dft4<T, INV>(b);
+#pragma unroll
+    for (int s0 = 0; s0 < 4; ++s0) v[s1 + 4 * s0] = b[s0];
+  }
+}
+
 template <typename T, int R, bool INV> __device__ __forceinline__ void dft_r(cx<T>* v) {
   if constexpr (R == 2) dft2<T, INV>(v);
   else if constexpr (R == 3) dft3<T, INV>(v);
   else if constexpr (R == 4) dft4<T, INV>(v);
   else if constexpr (R == 6) dft6<T, INV>(v);
-  else dft8<T, INV>(v);
+  else if constexpr (R == 8) dft8<T, INV>(v);
+  else if constexpr (R == 12) dft12<T, INV>(v);
+  else dft16<T, INV>(v);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -115,7 +180,9 @@ template <typename T, int R, bool INV> __device__ __forceinline__ void dft_r(cx<
 // ---------------------------------------------------------------------------------------
 // Physical LDS slot of element i: with PAD > 0 one spare slot follows every 2^PAD elements,
 // which breaks the power-of-two strides of the first Stockham stages across LDS banks.
-template <int PAD> __device__ __forceinline__ int padi(int i) { return PAD > 0 ? i + (i >> PAD) : i; }
+template <int PAD> __host__ __device__ __forceinline__ constexpr int padi(int i) {
+  return PAD > 0 ? i + (i >> PAD) : i;
+}
 
 template <typename T, int E, int R, bool INV, int PAD>
 __device__ __forceinline__ void stockham_stage(cx<T>* lds, int off, int es, int L, int m, int t, int Pt,
@@ -154,9 +221,8 @@ __device__ __forceinline__ void stockham_stage(cx<T>* lds, int off, int es, int 
 
 // ---------------------------------------------------------------------------------------
 // Compile-time Stockham FFT for L = 2^a 3^b with the line held in registers on entry and
-// exit.  At each stage the first of the radices 8, 6, 4, 3, 2 that divides both E and the
-// remaining length (the order the host's schedules use); spans, strides and twiddle offsets
-// are constants.  Element e of the register array u is position t + PT*e of the line (PT = L/E
+// exit.  At each stage the first of the radices 12, 8, 6, 4, 3, 2 that divides both E and the
+// remaining length, or 16 where that saves a stage (E = 16 and 16, 256 or 1024 left); spans, strides and twiddle offsets are constants.  Element e of the register array u is position t + PT*e of the line (PT = L/E
 // threads per line, this thread number t).  The first stage reads its inputs straight from
 // u and the last stage's outputs are exactly the positions t + PT*e again, so only the
 // exchanges between stages go through LDS (at lds[off + padi<PAD>(i)*es]).
@@ -169,7 +235,9 @@ __device__ __forceinline__ void stockham_stage(cx<T>* lds, int off, int es, int 
 // a wavefront-level ordering (LDS operations of one wave complete in issue order).
 // ---------------------------------------------------------------------------------------
 __host__ __device__ constexpr int ct_radix(int e, int rem) {
-  return (e % 8 == 0 && rem % 8 == 0)   ? 8
+  return (e % 16 == 0 && (rem == 16 || rem == 256 || rem == 1024)) ? 16
+         : (e % 12 == 0 && rem % 12 == 0) ? 12
+         : (e % 8 == 0 && rem % 8 == 0)   ? 8
          : (e % 6 == 0 && rem % 6 == 0) ? 6
          : (e % 4 == 0 && rem % 4 == 0) ? 4
          : (e % 3 == 0 && rem % 3 == 0) ? 3
@@ -229,14 +297,90 @@ template <bool WAVE> __device__ __forceinline__ void ct_sync() {
   }
 }
 
+// Spare slots of one exchange: element i sits at i + a (i >> s).
+struct Pad {
+  int s, a;
+  __host__ __device__ constexpr int operator()(int i) const { return i + a * (i >> s); }
+};
+// Most lanes of a group that fall on one LDS bank (a slot of 8 or 16 bytes covers 2 or 4 of the 64 banks;
+// 32 or 16 lanes are served at a time).
+__host__ __device__ constexpr int ct_hits(Pad pad, int banks, int PT, int t0, bool scatter, int M, int R) {
+  int count[32] = {};
+  int worst = 0;
+  for (int i = 0; i < (PT < banks ? PT : banks); ++i) {
+    const int t = t0 + i, b = pad(scatter ? (t - t % M) * R + t % M : t) % banks;
+    worst = ++count[b] > worst ? count[b] : worst;
+  }
+  return worst;
+}
+// Whether the slot of i + K is that of i plus the constant pad(K), for every i of a stage: then one
+// address register and immediate offsets serve it.  Writes: i mod M R < M and K = s M < M R.  Reads: i is
+// any position, so K must be a multiple of the spacing.
+__host__ __device__ constexpr bool ct_sep_w(Pad p, int M, int MR) {
+  const int span = 1 << p.s;
+  return p.a == 0 || M % span == 0 || (span % M == 0 && (MR % span == 0 || span % MR == 0));
+}
+__host__ __device__ constexpr bool ct_sep_r(Pad p, int K) { return p.a == 0 || K % (1 << p.s) == 0; }
+// The spare slots of the exchange after the stage that ends at span X (the writes of that stage, the
+// reads of the next) of a length-L line in LDS slots of one element: those with the fewest bank
+// conflicts, then constant offsets, then the least space (at most one quarter more).
+__host__ __device__ constexpr Pad ct_exchange_pad(int bytes, int E, int L, int X) {
+  const int banks = 256 / bytes, PT = L / E;
+  int M = 1, R = ct_radix(E, L);
+  while (M * R < X) {
+    M *= R;
+    R = ct_radix(E, L / M);
+  }
+  const int R2 = ct_radix(E, L / X);
+  Pad best{0, 0};
+  int best_cost = 1 << 30;
+  for (int s = 1; s <= 9; ++s)
+    for (int a = 0; a <= 8; ++a) {
+      const Pad p{s, a};
+      if (a * ((L - 1) >> s) * 4 > L || (a == 0 && s > 1)) continue;
+      int cost = 0;
+      for (int t0 = 0; t0 < PT && t0 <= banks; t0 += banks)
+        cost += 64 * (ct_hits(p, banks, PT, t0, true, M, R) + ct_hits(p, banks, PT, t0, false, M, R));
+      bool sep = ct_sep_w(p, M, M * R) && ct_sep_r(p, L / R2);
+      if (E / R2 > 1) sep = sep && ct_sep_r(p, PT);
+      cost += (sep ? 0 : 32) + a * ((L - 1) >> s) * 16 / L;
+      if (cost < best_cost) {
+        best_cost = cost;
+        best = p;
+      }
+    }
+  return best;
+}
+// PAD of the compile-time transforms: padi's, or AUTO_PAD for the choice above (es = 1 only).
+constexpr int AUTO_PAD = 64;
+template <typename T, int E, int PAD, int L, int X> __host__ __device__ constexpr Pad ct_pad_of() {
+  if constexpr (PAD == AUTO_PAD) return ct_exchange_pad((int)sizeof(cx<T>), E, L, X);
+  else if constexpr (PAD > 0) return Pad{PAD, 1};
+  else return Pad{0, 0};
+}
+// LDS slots of a line with AUTO_PAD.
+template <typename T, int E, int L> __host__ __device__ constexpr int ct_line_slots() {
+  int slots = L;
+  for (int m = ct_radix(E, L); m < L; m *= ct_radix(E, L / m)) {
+    const int n = ct_exchange_pad((int)sizeof(cx<T>), E, L, m)(L - 1) + 1;
+    slots = n > slots ? n : slots;
+  }
+  return slots;
+}
+
 // Stage of span M: inputs v[q*R + s] = x[b + s*L/R], b = t + q*PT.
 template <typename T, int E, int PAD, int L, int M>
 __device__ __forceinline__ void ct_gather(const cx<T>* lds, int off, int es, int t, cx<T>* v) {
   constexpr int R = ct_radix(E, L / M), PT = L / E, NB = E / R, LR = L / R;
+  constexpr Pad pad = ct_pad_of<T, E, PAD, L, M>();
+  const cx<T>* p = lds + off + pad(t) * es;
 #pragma unroll
   for (int q = 0; q < NB; ++q)
 #pragma unroll
-    for (int s = 0; s < R; ++s) v[q * R + s] = lds[off + padi<PAD>(t + q * PT + s * LR) * es];
+    for (int s = 0; s < R; ++s) {
+      if (ct_sep_r(pad, q * PT + s * LR)) v[q * R + s] = p[pad(q * PT + s * LR) * es];
+      else v[q * R + s] = lds[off + pad(t + q * PT + s * LR) * es];
+    }
 }
 template <typename T, int E, bool INV, int L, int M>
 __device__ __forceinline__ void ct_butterflies(int t, cx<T>* v, const cx<T>* twst) {
@@ -259,13 +403,18 @@ __device__ __forceinline__ void ct_butterflies(int t, cx<T>* v, const cx<T>* tws
 template <typename T, int E, int PAD, int L, int M>
 __device__ __forceinline__ void ct_scatter(cx<T>* lds, int off, int es, int t, const cx<T>* v) {
   constexpr int R = ct_radix(E, L / M), PT = L / E, NB = E / R;
+  constexpr Pad pad = ct_pad_of<T, E, PAD, L, M * R>();
 #pragma unroll
   for (int q = 0; q < NB; ++q) {
     const int b = t + q * PT;
     const int k = b % M;
     const int base = (b - k) * R + k;
+    cx<T>* p = lds + off + pad(base) * es;
 #pragma unroll
-    for (int s = 0; s < R; ++s) lds[off + padi<PAD>(base + s * M) * es] = v[q * R + s];
+    for (int s = 0; s < R; ++s) {
+      if (ct_sep_w(pad, M, M * R)) p[pad(s * M) * es] = v[q * R + s];
+      else lds[off + pad(base + s * M) * es] = v[q * R + s];
+    }
   }
 }
 template <typename T, int E, bool INV, int PAD, int L, bool WAVE, int M>
@@ -300,7 +449,36 @@ __device__ __forceinline__ void ct_fft_regs(cx<T>* lds, int off, int es, int t, 
     for (int s = 0; s < RL; ++s) u[q + s * NBL] = v[q * RL + s];
 }
 
-// Same with the input line already in LDS (filled and made visible by the caller).
+// ct_fft_regs in two parts, so that a caller can refill the registers it loaded the line into while the
+// later stages run.
+template <typename T, int E, bool INV, int L>
+__device__ __forceinline__ void ct_first_stage(const cx<T>* u, cx<T>* v) {
+  constexpr int R0 = ct_radix(E, L), NB0 = E / R0;
+#pragma unroll
+  for (int q = 0; q < NB0; ++q) {
+#pragma unroll
+    for (int s = 0; s < R0; ++s) v[q * R0 + s] = u[q + s * NB0];
+    dft_r<T, R0, INV>(&v[q * R0]);
+  }
+}
+template <typename T, int E, bool INV, int PAD, int L, bool WAVE>
+__device__ __forceinline__ void ct_later_stages(cx<T>* lds, int off, int t, cx<T>* v, cx<T>* u, const cx<T>* twst) {
+  constexpr int R0 = ct_radix(E, L);
+  constexpr int RL = ct_last_radix(E, L), NBL = E / RL;
+  if constexpr (R0 < L) {
+    ct_sync<WAVE>();
+    ct_scatter<T, E, PAD, L, 1>(lds, off, 1, t, v);
+    ct_sync<WAVE>();
+    ct_gather<T, E, PAD, L, R0>(lds, off, 1, t, v);
+    ct_rest<T, E, INV, PAD, L, WAVE, R0>(lds, off, 1, t, v, twst);
+  }
+#pragma unroll
+  for (int q = 0; q < NBL; ++q)
+#pragma unroll
+    for (int s = 0; s < RL; ++s) u[q + s * NBL] = v[q * RL + s];
+}
+
+// Same as ct_fft_regs with the input line already in LDS (filled and made visible by the caller).
 template <typename T, int E, bool INV, int PAD, int L, bool WAVE>
 __device__ __forceinline__ void ct_fft_lds_in(cx<T>* lds, int off, int es, int t, cx<T>* u, const cx<T>* twst) {
   constexpr int RL = ct_last_radix(E, L), NBL = E / RL;
@@ -349,34 +527,24 @@ __device__ __forceinline__ void lds_fft(cx<T>* lds, int off, int es, int L, uint
 constexpr int YLM_LMAX = 16;
 constexpr int YLM_STRIDE = 2 * YLM_LMAX + 2;
 
-// Running evaluation of real Y_lm at NV points over a sequence of fields.  The state keeps
-// (ux + i uy)^am and the recurrence pair (q_{l-1}^am, q_l^am) of the last field, so a field
-// with the same |m| and a larger l continues the recurrence, the -m partner of a field costs
-// nothing, and a field with |m| one larger costs one complex multiply plus a restart of the
-// recurrence.  Fields in any other order restart from scratch (still correct).  Control flow
-// depends only on (l, m), which are wave-uniform.
 // Cartesian decomposition (Sec. 2.1, the monomial form the spherical-harmonic expansion
 // replaces): a field of degree p is weighted by the monomial u_x^i u_y^j u_z^(p-i-j), its
 // index packed as code = 32 i + j.  out = coef * monomial for NV directions.
 __host__ __device__ constexpr int cart_code(int i, int j) { return 32 * i + j; }
 
-template <typename T, int NV>
-__device__ __forceinline__ void monomial_eval(int p, int code, T coef, const T* ux, const T* uy, const T* uz,
-                                              T* out) {
-  const int i = code >> 5, j = code & 31, k = p - i - j;
+// dir(v, x, y, z) gives direction v.
+template <typename T, int NV, typename DIR>
+__device__ __forceinline__ void monomial_eval(int p, int code, T coef, DIR dir, T* out) {
+  const int i = code >> 5, j = code & 31;
 #pragma unroll
   for (int v = 0; v < NV; ++v) out[v] = coef;
-  for (int q = 0; q < i; ++q) {
+  for (int q = 0; q < p; ++q) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) out[v] *= ux[v];
-  }
-  for (int q = 0; q < j; ++q) {
-#pragma unroll
-    for (int v = 0; v < NV; ++v) out[v] *= uy[v];
-  }
-  for (int q = 0; q < k; ++q) {
-#pragma unroll
-    for (int v = 0; v < NV; ++v) out[v] *= uz[v];
+    for (int v = 0; v < NV; ++v) {
+      T x, y, z;
+      dir(v, x, y, z);
+      out[v] *= q < i ? x : q < i + j ? y : z;
+    }
   }
 }
 
@@ -389,38 +557,41 @@ __device__ __forceinline__ int multinomial(int p, int code) {
   return (int)c;
 }
 
-template <typename T, int NV> struct YRun {
+// Running evaluation of the real Y_lm at NV points over a sequence of (l, |m|).  The state keeps
+// c = c0 (ux + i uy)^am, where c0 is what the caller put there (1, or the field value the
+// harmonics weight), and the recurrence pair (q_{l-1}^am, q_l^am), so that
+// Y_{l,+m} c0 = q1 cr and Y_{l,-m} c0 = q1 ci (c0 real).  An entry with the same |m| and a larger l
+// continues the recurrence, one with a larger |m| costs complex multiplies and a restart of the
+// recurrence; |m| may only grow between resets of the state.  Control flow depends only on
+// (l, |m|), which are wave-uniform.  f scales the start of the recurrence (every q is linear in it).
+template <typename T, int NV> struct HRun {
   T cr[NV], ci[NV], q0[NV], q1[NV];
   int am, l;
 };
 
-template <typename T, int NV> __device__ __forceinline__ void yrun_init(YRun<T, NV>& s) {
-  s.am = -1;
+// The caller sets cr, ci; this starts the state at |m| = 0 with no degree evaluated.
+template <typename T, int NV> __device__ __forceinline__ void hrun_init(HRun<T, NV>& s) {
+  s.am = 0;
   s.l = -1;
 }
 
-// PAIRS: advance the recurrence two degrees per iteration (fewer register copies, more
-// registers live); off for register-bound callers.
-template <typename T, int NV, bool PAIRS = true>
-__device__ __forceinline__ void yrun_eval(YRun<T, NV>& s, int ell, int m, const T* ux, const T* uy, const T* uz,
-                                          T* out, const T* __restrict__ tab) {
-  const int am = m < 0 ? -m : m;
-  if (am != s.am || ell < s.l) {
-    if (s.am < 0 || am < s.am) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) { s.cr[v] = T(1); s.ci[v] = T(0); }
-      s.am = 0;
-    }
+// dir(v, &x, &y, &z): the unit vector of point v.
+template <typename T, int NV, bool TIGHT = false, typename DIR>
+__device__ __forceinline__ void hrun_to(HRun<T, NV>& s, int ell, int am, T f, const T* __restrict__ tab, DIR dir) {
+  if (am != s.am || s.l < am || ell < s.l) {
     for (int j = s.am; j < am; ++j) {
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        const T nr = s.cr[v] * ux[v] - s.ci[v] * uy[v];
-        s.ci[v] = s.cr[v] * uy[v] + s.ci[v] * ux[v];
+        T x, y, z;
+        dir(v, x, y, z);
+        const T nr = s.cr[v] * x - s.ci[v] * y;
+        s.ci[v] = s.cr[v] * y + s.ci[v] * x;
         s.cr[v] = nr;
+        if (TIGHT) __builtin_amdgcn_sched_barrier(0);
       }
     }
     s.am = am;
-    const T c0 = tab[am * YLM_STRIDE];
+    const T c0 = tab[am * YLM_STRIDE] * f;
 #pragma unroll
     for (int v = 0; v < NV; ++v) { s.q1[v] = c0; s.q0[v] = T(0); }
     s.l = am;
@@ -428,34 +599,33 @@ __device__ __forceinline__ void yrun_eval(YRun<T, NV>& s, int ell, int m, const 
   const T* c = tab + am * YLM_STRIDE;
   int l = s.l + 1;
   // two degrees per iteration with the pair's roles swapped in between (no register copies)
-  for (; PAIRS && l + 1 <= ell; l += 2) {
+  for (; l + 1 <= ell; l += 2) {
     const int j = l - am;
     const T a1 = c[2 * j - 1], b1 = c[2 * j];  // b = 0 for j = 1
     const T a2 = c[2 * j + 1], b2 = c[2 * j + 2];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      s.q0[v] = a1 * uz[v] * s.q1[v] - b1 * s.q0[v];  // q_l
-      s.q1[v] = a2 * uz[v] * s.q0[v] - b2 * s.q1[v];  // q_{l+1}
+      T x, y, z;
+      dir(v, x, y, z);
+      s.q0[v] = a1 * z * s.q1[v] - b1 * s.q0[v];  // q_l
+      s.q1[v] = a2 * z * s.q0[v] - b2 * s.q1[v];  // q_{l+1}
+      if (TIGHT) __builtin_amdgcn_sched_barrier(0);
     }
   }
-  for (; l <= ell; ++l) {
+  if (l <= ell) {
     const int j = l - am;
     const T a = c[2 * j - 1], b = c[2 * j];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      const T q2 = a * uz[v] * s.q1[v] - b * s.q0[v];
+      T x, y, z;
+      dir(v, x, y, z);
+      const T q2 = a * z * s.q1[v] - b * s.q0[v];
       s.q0[v] = s.q1[v];
       s.q1[v] = q2;
+      if (TIGHT) __builtin_amdgcn_sched_barrier(0);
     }
   }
   s.l = ell;
-  if (m < 0) {  // m is the same for the whole wave
-#pragma unroll
-    for (int v = 0; v < NV; ++v) out[v] = s.q1[v] * s.ci[v];
-  } else {
-#pragma unroll
-    for (int v = 0; v < NV; ++v) out[v] = s.q1[v] * s.cr[v];
-  }
 }
 
 // Atomic add to an LDS location (native ds_add_f32 / ds_add_f64; a plain atomicAdd through a

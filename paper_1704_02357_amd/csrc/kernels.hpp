@@ -22,16 +22,36 @@ struct FftShape {
   int nst_post;
   int tile_post;    // columns per post-pass tile
   int cus;          // compute units of the device (0: unknown)
-  int fpad;         // extra elements per kz plane of a field buffer [kz][x][y]: the plane
-                    // stride n n + fpad is then not a power of two
+  bool col_builtin;  // e_col and tile are the built-in choice: the column passes run the
+                     // kernels compiled for the side
+};
+
+// Field buffers (the weighted fields after their z transform) are kz-major, [kz][x][y] with n/2 kz planes
+// of n n complex values plus 256 bytes: a power-of-two plane stride would put the pre-pass's stores,
+// which go to every plane, on few HBM channels.
+template <typename T> __host__ __device__ constexpr size_t field_plane_stride(int n) {
+  return (size_t)n * n + 128 / sizeof(T);
+}
+// One record of the field tables (device).  A pre-pass entry: the buffers p0 and p1 of a pair (p1 null:
+// a field alone), l (or degree), m (or monomial code), the partner's code m2; the column pass
+// takes the same entries.  A post-pass line: its field's buffer p0, l, m and the multipole's slot.
+struct FieldRec {
+  void* p0;
+  void* p1;
+  int l, m, m2, slot;
 };
 
 // Bytes of LDS of the z-pass and column-pass blocks of a shape.
 size_t zpass_smem_bytes(const FftShape& fs, bool fp64);
 size_t colpass_smem_bytes(const FftShape& fs, bool fp64);
 
-// LDS bytes of a post-pass block without its histograms.
-size_t xpost_base_bytes(const FftShape& fs, bool fp64);
+// The post-pass of a side: kz lines per tile, threads per block, persistent blocks per CU and LDS
+// bytes without histograms and thresholds.  false: no such side.
+struct PostGeometry {
+  int tp, threads, per_cu;
+  size_t smem;
+};
+template <typename T> bool post_geometry(int n, PostGeometry* g);
 
 // Orthogonal matrix (rows r[0..2], r[3..5], r[6..8]) applied to every unit vector, node
 // direction and wave vector alike, before harmonics or monomials are evaluated.  The sums
@@ -49,8 +69,11 @@ struct Frame {
 
 struct BinSpec {
   const long long* thr;  // device, nb+1 integer thresholds on |n|^2
+  const int* thr32;      // the same, clamped to the int range (no |n|^2 of a mesh reaches it)
   int nb;
-  int hist_copies;       // per-block histogram copies (1 .. number of waves)
+  int hist_copies;       // per-block histogram copies
+  int turns;             // wavefronts per copy (they add one after the other)
+  int thr_lds;           // stage the thresholds in LDS
 };
 
 // Catalog sums: out2[0] = sum w^2, out2[1] = sum w^2 nbar, *wmax = max |w| (w, nbar may be
@@ -94,12 +117,15 @@ template <typename T>
 hipError_t launch_zfwd(const FftShape& fs, const T* in0, const T* in1, void* out0, void* out1, int nbuf,
                        const void* tw, hipStream_t s);
 
-// Column transform of nbuf buffers in place: half spectra [x][y][kz] along y (axis = 1) or x
-// (axis = 0); fields = true: kz-major field buffers [kz][x][y] (kz planes of n n + fs.fpad
-// elements) along x.
+// Column transform of nbuf half spectra [x][y][kz] in place along y (axis = 1) or x (axis = 0).
 template <typename T>
 hipError_t launch_col(const FftShape& fs, void* const* bufs_dev, int nbuf, int axis, bool inverse,
-                      const void* tw, hipStream_t s, bool fields = false);
+                      const void* tw, hipStream_t s);
+// Forward transform along x of the field buffers of `nent` entries in place, their first `planes` kz
+// planes; rows whose modes all have |n|^2 >= tmax are left unwritten.  Separates the fields of a pair.
+template <typename T>
+hipError_t launch_col_fields(const FftShape& fs, const FieldRec* ents_dev, int nent, int planes, int tmax,
+                             const void* tw, hipStream_t s);
 
 // x-pass of the forward transforms of the two painted meshes, interlace combine,
 // compensation and Nyquist zeroing; writes C and, when g_out != null, G = C inverse-
@@ -108,28 +134,32 @@ template <typename T>
 hipError_t launch_xcombine(const FftShape& fs, void* s1, void* s2, void* c_out, void* g_out, int interlaced,
                            int compensated, const void* invw, const void* phase, const void* tw, hipStream_t s);
 
-// Inverse z (half-complex to real) of G, scaled to D_c, then for every field f in the group
-// the Y_lm(xhat)-weighted forward transform along z into the kz-major field buffer bufs[f]
-// ([kz][x][y], kz planes of n n + fs.fpad elements).  Needs fs.zlines to divide n.  If real_in != null the
-// field D_c is read directly from that real mesh instead.  If real_out != null D_c is also
-// written there.  basis 1 (Cartesian decomposition): field f is weighted by the monomial
-// xhat^a of degree fields[4f+1] and index code fields[4f+2] instead of Y_lm(xhat).
+// Inverse z transform (half-complex to real) of G, scaled, into a real mesh.
 template <typename T>
-hipError_t launch_zpre(const FftShape& fs, const void* g_in, const T* real_in, T* real_out, void* const* bufs_dev,
-                       int nf, const int* fields_dev, double scale, const double* off, double h, const void* ytab,
-                       const void* tw, const Frame& frame, int basis, hipStream_t s);
+hipError_t launch_zinv(const FftShape& fs, const void* g_in, T* real_out, double scale, const void* tw,
+                       hipStream_t s);
 
-// Last transform pass of every field of the group (along y over the kz-major field buffers),
-// sum over m of Y_lm(khat) B_lm per multipole slot, product with C and binning.  Odd l
-// (spherical basis) are binned as Im[C conj (sum)] instead of Re.  Per block the partial sums are rows of nb bins:
+// Inverse z of G, scaled to D_c (or D_c read from real_in != null), then for every entry of the group
+// the Y_lm(xhat)-weighted forward transform along z into the field buffers, kz planes below
+// kz_live only.  basis 1 (Cartesian decomposition): weights are the monomials xhat^a of degree l and
+// index code m instead of Y_lm(xhat).  Entries must come with |m| ascending.
+template <typename T>
+hipError_t launch_zpre(const FftShape& fs, const void* g_in, const T* real_in, int nent, const FieldRec* ents_dev,
+                       double scale, const double* off, double h, const void* ytab,
+                       const void* tw, const Frame& frame, int basis, int kz_live, hipStream_t s);
+
+// Last transform pass of every field of the group (along y), sum over m of Y_lm(khat) B_lm per
+// multipole slot, product with C and binning over the listed tiles (x << 16 | kz0).  Odd l
+// (spherical basis) are binned as Im[C conj (sum)] instead of Re.  Lines come slot by slot, |m|
+// ascending within a slot.  Per block the partial sums are rows of nb bins:
 // [count, sum |k|, sum |C|^2] when with_l0, then one row of sum 4 pi Y Re[C conj B] per slot.
 // basis 1: the slot sums (p!/a!) khat^a B_a over the monomials a of one degree p, and its row
 // holds sum Re[C conj (that sum)] without the 4 pi.
 template <typename T>
-hipError_t launch_xpost(const FftShape& fs, void* const* bufs_dev, int nf, const int* fields_dev, int nslots,
-                        int with_l0, const void* c_in, const void* ytab, const BinSpec& bs, double kf,
-                        double* partial, int* nblocks_out, const void* tw, const Frame& frame, int basis,
-                        hipStream_t s);
+hipError_t launch_xpost(const FftShape& fs, int nrecs, const FieldRec* recs_dev, int nslots, int with_l0,
+                        const void* c_in, const void* ytab, const BinSpec& bs, double kf,
+                        double* partial, int nblocks, const void* tw, const Frame& frame, int basis,
+                        const unsigned* tiles_dev, int ntiles, hipStream_t s);
 
 // out[map[v]] (+)= sum_b partial[b*nvals + v] (map null -> identity), fixed order.
 hipError_t launch_reduce(const double* partial, int nblocks, int nvals, double* out, const int* map, int accumulate,
@@ -144,9 +174,5 @@ hipError_t launch_kmu(const FftShape& fs, const void* c_in, const double* los, c
 // P = sum / (I count) - S (NaN when empty) and the integer counts.
 hipError_t launch_kmu_finish(const double* sums, int ncells, double norm_I, double shot, double* pk, long long* nm,
                              hipStream_t s);
-
-int xpass_blocks(const FftShape& fs);
-int xpass_threads(const FftShape& fs);
-int post_blocks(const FftShape& fs);
 
 }  // namespace pkm

@@ -6,9 +6,8 @@
 //   of C) -> inverse y of G,
 // leaving C (the combined field, F_0 of eq. Pell-ours) and G (D_c, transformed along z only)
 // resident.  pkm_compute_multipoles then runs, per group of (l, m) fields,
-//   zpre (inverse z of G = D_c, Y_lm(xhat) weighting, forward z per field) -> column pass
-//   per field (y for FP32, x for FP64) -> xpost (the remaining axis, sum_m Y_lm(khat) B_lm,
-//   product with C, binning)
+//   zpre (inverse z of G = D_c, Y_lm(xhat) weighting, forward z of two fields at a time) -> column
+//   pass along x per field buffer -> xpost (y, sum_m Y_lm(khat) B_lm, product with C, binning)
 // and one fixed-order reduction per group.  The l = 0 bin (|C|^2) and the mode counts are
 // taken in the first xpost pass.  pkm_prepare / pkm_enqueue / pkm_finish issue the same
 // work asynchronously; runtime.hip builds batches and the serving loop on them.
@@ -32,9 +31,10 @@
 
 using namespace pkm;
 
-// One field group of a multipole request: field-table offsets, reduce map, histogram shape.
+// One field group of a multipole request: its pre-pass entries and post-pass lines in the field
+// tables, reduce map, histogram shape.
 struct GroupCfg {
-  int nf = 0, fofs = 0, pofs = 0, mofs = 0, nv = 0, nslots = 0, copies = 1;
+  int nf = 0, fofs = 0, nent = 0, pofs = 0, mofs = 0, nv = 0, nslots = 0, copies = 1, turns = 1;
 };
 struct ComputeCfg {
   int ell_max = -1;
@@ -44,6 +44,9 @@ struct ComputeCfg {
   std::vector<double> edges;
   int nb = 0, total_vals = 0, nfields_total = 0;
   std::vector<GroupCfg> groups;
+  // what the last k edge leaves of the spectrum: |n|^2 below tmax, so many kz planes of a field buffer
+  // and post-pass tiles
+  int tmax = 0, kz_live = 0, ntiles = 0, post_blocks = 1, thr_lds = 1;
 };
 
 struct pkm_plan {
@@ -75,7 +78,7 @@ struct pkm_plan {
   hipEvent_t done = nullptr;
   int64_t pend_nd = 0, pend_nr = 0;
   bool pending_async = false;
-  int* ftab_dev = nullptr;    // (l, m, slot) per field, all groups
+  FieldRec* ftab_dev = nullptr;  // pre-pass entries and post-pass lines, all groups
   int ftab_cap = 0;
   int* map_dev = nullptr;     // reduce map per value
   int map_cap = 0;
@@ -83,8 +86,10 @@ struct pkm_plan {
   void* ytab = nullptr;
   void* invw = nullptr;
   void* phase = nullptr;
-  long long* thr_dev = nullptr;
+  int* thr_dev = nullptr;
   int thr_cap = 0;
+  unsigned* tiles_dev = nullptr;  // post-pass tiles of the prepared request
+  int tiles_cap = 0;
   double* partial = nullptr;
   size_t partial_cap = 0;  // doubles
   double* out_dev = nullptr;
@@ -348,13 +353,35 @@ std::vector<double> legendre_coeffs(int l) {
   return b;
 }
 
-// Bytes of one kz-major field buffer [kz][x][y]: n/2 kz planes of n n + fpad complex values.
-size_t field_bytes(const pkm_plan* pl) {
-  return pl->mesh_bytes + (size_t)(pl->p.nmesh / 2) * pl->fs.fpad * 2 * pl->es;
+// Bytes of one field buffer (kernels.hpp).
+size_t field_bytes(int n, bool fp64) {
+  return (size_t)(n / 2) * (fp64 ? sizeof(double2) * field_plane_stride<double>(n)
+                                 : sizeof(float2) * field_plane_stride<float>(n));
+}
+
+PostGeometry post_geometry_of(int n, bool fp64) {
+  PostGeometry g{};
+  if (fp64) (void)post_geometry<double>(n, &g); else (void)post_geometry<float>(n, &g);
+  return g;
+}
+
+// Persistent post-pass blocks for a number of tiles: as many as the registers leave room for, in
+// multiples of 8 (one share of the tiles per XCD) where there are that many.
+int post_blocks_for(const PostGeometry& g, int cus, int ntiles) {
+  const int n = std::max(1, std::min(ntiles, g.per_cu * (cus > 0 ? cus : 256)));
+  return n >= 8 ? n / 8 * 8 : n;
+}
+
+// LDS base of the limit on k bins: a request is refused when this, the thresholds and five rows of one
+// histogram exceed the LDS of a CU, and a deterministic one when its histograms exceed 150 KB with one
+// per wavefront of tile_post lines of e_post elements per thread.  The kernels need less.
+size_t bin_limit_base(const FftShape& fs, bool fp64) {
+  const size_t n = fs.n;
+  return (fp64 ? sizeof(double2) : sizeof(float2)) * (fs.tile_post * (n + n / 8 + 1) + fs.tile_post * n + n);
 }
 
 void ensure_fields(pkm_plan* pl, int want) {
-  while ((int)pl->fields.size() < want) pl->fields.push_back(dalloc(pl, field_bytes(pl)));
+  while ((int)pl->fields.size() < want) pl->fields.push_back(dalloc(pl, field_bytes(pl->p.nmesh, pl->fp64)));
   const int need_ptr = (int)pl->fields.size() + 8;
   if (pl->ptr_cap < need_ptr) {
     dfree(pl, pl->ptrs_dev);
@@ -605,10 +632,34 @@ void prepare_compute(pkm_plan* pl, int ell_max, const double* k_edges, int n_edg
   }
   if (pl->thr_cap < n_edges) {
     dfree(pl, pl->thr_dev);
-    pl->thr_dev = (long long*)dalloc(pl, sizeof(long long) * n_edges);
+    pl->thr_dev = (int*)dalloc(pl, sizeof(int) * n_edges);
     pl->thr_cap = n_edges;
   }
-  check_hip(pl, hipMemcpy(pl->thr_dev, thr.data(), sizeof(long long) * n_edges, hipMemcpyHostToDevice), "thr");
+  // (|n|^2 of a mesh is below 2^20: clamped thresholds order the same)
+  std::vector<int> thr32(n_edges);
+  for (int i = 0; i < n_edges; ++i) thr32[i] = (int)std::min<long long>(thr[i], 1 << 30);
+  check_hip(pl, hipMemcpy(pl->thr_dev, thr32.data(), sizeof(int) * n_edges, hipMemcpyHostToDevice), "thr");
+  // the part of the spectrum below the last edge: post-pass tiles (x, kz0), x-major
+  const PostGeometry geo = post_geometry_of(n, pl->fp64);
+  cc.tmax = thr32[nb];
+  std::vector<unsigned> tiles;
+  for (int x = 0; x < n; ++x) {
+    if (x == n / 2) continue;
+    const int fx = x < n / 2 ? x : x - n;
+    for (int kz0 = 0; kz0 < n / 2 && fx * fx + kz0 * kz0 < cc.tmax; kz0 += geo.tp) {
+      tiles.push_back((unsigned)x << 16 | (unsigned)kz0);
+      cc.kz_live = std::max(cc.kz_live, std::min(kz0 + geo.tp, n / 2));
+    }
+  }
+  cc.ntiles = (int)tiles.size();
+  cc.post_blocks = post_blocks_for(geo, pl->fs.cus, cc.ntiles);
+  if (pl->tiles_cap < cc.ntiles) {
+    dfree(pl, pl->tiles_dev);
+    pl->tiles_dev = (unsigned*)dalloc(pl, sizeof(unsigned) * tiles.size());
+    pl->tiles_cap = cc.ntiles;
+  }
+  if (cc.ntiles)
+    check_hip(pl, hipMemcpy(pl->tiles_dev, tiles.data(), sizeof(unsigned) * tiles.size(), hipMemcpyHostToDevice), "tiles");
   // fields and groups
   struct F { int l, m, slot; };
   std::vector<std::vector<F>> groups;
@@ -633,14 +684,18 @@ void prepare_compute(pkm_plan* pl, int ell_max, const double* k_edges, int n_edg
         for (int i = 0; i <= l; ++i)
           for (int j = 0; i + j <= l; ++j) add(l, 32 * i + j);
       } else {
-        for (int m = -l; m <= l; ++m) add(l, m);
+        add(l, 0);
+        for (int m = 1; m <= l; ++m) {  // +m and -m side by side: they pair up in one group
+          add(l, m);
+          add(l, -m);
+        }
       }
     }
     if (!cur.empty()) groups.push_back(cur);
     if (groups.empty()) groups.push_back({});  // l = 0 only
   }
   const int rows = 2 + ell_rows(ell_max, basis);  // count, ksum, Q0, then Q2, Q4, ... (or Q1, Q2, ...)
-  const size_t col_lds = xpost_base_bytes(pl->fs, sizeof(T) == 8) + sizeof(long long) * (size_t)n_edges;
+  const size_t col_lds = bin_limit_base(pl->fs, sizeof(T) == 8) + sizeof(long long) * (size_t)n_edges;
   if (col_lds + sizeof(double) * 5 * (size_t)nb > 160 * 1024) {
     pl->err = "too many k bins for one pass";
     throw Fail{PKM_EINVAL};
@@ -651,28 +706,42 @@ void prepare_compute(pkm_plan* pl, int ell_max, const double* k_edges, int n_edg
     pl->out_dev = (double*)dalloc(pl, sizeof(double) * total_vals);
     pl->out_cap = total_vals;
   }
-  // Per group two field tables of (buffer, l, m, slot): the pre-pass walks the fields
-  // |m|-major (|m| ascending, then l, +m before -m) so the harmonic recurrence of one field
-  // continues from the previous one; the post-pass walks them l-major (slots contiguous),
-  // |m| ascending with +m before -m.  Buffer b of a group holds its b-th field (l-major).
-  std::vector<int> ftab, maps;
+  // Per group two tables of records (kernels.hpp).  Buffer b of a group holds its b-th
+  // field.  Two fields of one multipole share a transform, +m and -m or two monomials (never of two
+  // multipoles: the rounding of P_l would then depend on ell_max); a field whose partner is in another
+  // group, or that has none, goes alone.  The pre-pass walks the entries |m|-major (|m| ascending, then
+  // l) so the harmonic recurrence of one continues from the previous one; the post-pass walks the fields
+  // slot by slot, |m| ascending.
+  std::vector<FieldRec> ftab;
+  std::vector<int> maps;
   for (size_t gi = 0; gi < groups.size(); ++gi) {
     const auto& g = groups[gi];
-    std::vector<int> idx(g.size());
-    for (size_t i = 0; i < g.size(); ++i) idx[i] = (int)i;
-    auto key_pre = [&](int i) {
-      return basis == 1 ? std::make_tuple(g[i].l, g[i].m, false) : std::make_tuple(std::abs(g[i].m), g[i].l, g[i].m < 0);
-    };
-    auto key_post = [&](int i) { return std::make_tuple(g[i].slot, std::abs(g[i].m), g[i].m < 0); };
-    std::vector<int> pre = idx, post = idx;
-    std::stable_sort(pre.begin(), pre.end(), [&](int a, int b) { return key_pre(a) < key_pre(b); });
-    std::stable_sort(post.begin(), post.end(), [&](int a, int b) { return key_post(a) < key_post(b); });
+    auto am = [](const FieldRec& e) { return std::abs(e.m); };
+    std::vector<FieldRec> pre;
+    for (size_t i = 0; i < g.size(); ++i) {
+      const F &f = g[i], *f2 = i + 1 < g.size() ? &g[i + 1] : nullptr;
+      const bool pair = f2 && f2->l == f.l && (basis == 1 || (f.m > 0 && f2->m == -f.m));
+      pre.push_back({pl->fields[i], pair ? pl->fields[i + 1] : nullptr, f.l, f.m, pair ? f2->m : 0, f.slot});
+      if (pair) ++i;
+    }
+    std::vector<FieldRec> post;
+    for (size_t i = 0; i < g.size(); ++i) post.push_back({pl->fields[i], nullptr, g[i].l, g[i].m, 0, g[i].slot});
+    if (basis != 1) {
+      std::stable_sort(pre.begin(), pre.end(), [&](const FieldRec& a, const FieldRec& b) {
+        return am(a) != am(b) ? am(a) < am(b) : a.l < b.l;
+      });
+      std::stable_sort(post.begin(), post.end(), [&](const FieldRec& a, const FieldRec& b) {
+        return a.slot != b.slot ? a.slot < b.slot : am(a) < am(b);
+      });
+    }
     GroupCfg gc;
     gc.nf = (int)g.size();
-    gc.fofs = (int)ftab.size() / 4;
-    for (int i : pre) { ftab.push_back(i); ftab.push_back(g[i].l); ftab.push_back(g[i].m); ftab.push_back(g[i].slot); }
-    gc.pofs = (int)ftab.size() / 4;
-    for (int i : post) { ftab.push_back(i); ftab.push_back(g[i].l); ftab.push_back(g[i].m); ftab.push_back(g[i].slot); }
+    gc.fofs = (int)ftab.size();
+    gc.nent = (int)pre.size();
+    ftab.insert(ftab.end(), pre.begin(), pre.end());
+    gc.pofs = (int)ftab.size();
+    ftab.insert(ftab.end(), post.begin(), post.end());
+    ftab.push_back(post.empty() ? FieldRec{} : post[0]);  // (the post-pass reads one record past a lone one)
     std::vector<int> slot_l;
     for (auto& f : g) if ((int)slot_l.size() <= f.slot) slot_l.push_back(f.l);
     const bool first = gi == 0;
@@ -686,20 +755,20 @@ void prepare_compute(pkm_plan* pl, int ell_max, const double* k_edges, int n_edg
     cc.groups.push_back(gc);
     cc.nfields_total += gc.nf;
   }
-  if (pl->ftab_cap < (int)ftab.size() + 4) {
+  ftab.push_back({});
+  if (pl->ftab_cap < (int)ftab.size()) {
     dfree(pl, pl->ftab_dev);
-    pl->ftab_dev = (int*)dalloc(pl, sizeof(int) * (ftab.size() + 4));
-    pl->ftab_cap = (int)ftab.size() + 4;
+    pl->ftab_dev = (FieldRec*)dalloc(pl, sizeof(FieldRec) * ftab.size());
+    pl->ftab_cap = (int)ftab.size();
   }
-  if (!ftab.empty())
-    check_hip(pl, hipMemcpy(pl->ftab_dev, ftab.data(), sizeof(int) * ftab.size(), hipMemcpyHostToDevice), "ftab");
+  check_hip(pl, hipMemcpy(pl->ftab_dev, ftab.data(), sizeof(FieldRec) * ftab.size(), hipMemcpyHostToDevice), "ftab");
   if (pl->map_cap < (int)maps.size()) {
     dfree(pl, pl->map_dev);
     pl->map_dev = (int*)dalloc(pl, sizeof(int) * maps.size());
     pl->map_cap = (int)maps.size();
   }
   check_hip(pl, hipMemcpy(pl->map_dev, maps.data(), sizeof(int) * maps.size(), hipMemcpyHostToDevice), "maps");
-  const int nblk = post_blocks(pl->fs);
+  const int nblk = cc.post_blocks;
   int max_nv = 0;
   for (auto& gc : cc.groups) max_nv = std::max(max_nv, gc.nv);
   if (pl->partial_cap < (size_t)nblk * max_nv) {
@@ -707,19 +776,25 @@ void prepare_compute(pkm_plan* pl, int ell_max, const double* k_edges, int n_edg
     pl->partial = (double*)dalloc(pl, sizeof(double) * (size_t)nblk * max_nv);
     pl->partial_cap = (size_t)nblk * max_nv;
   }
-  // histogram copies per block: one per wave when the LDS budget of two post-pass blocks per
-  // CU allows (the register budget allows no more than two)
-  // (deterministic mode: one per wave always, within the LDS of one block per CU, so that no
-  // two waves add to the same bin)
-  const int waves = ((n / pl->fs.e_post) * pl->fs.tile_post + 63) / 64;
-  const size_t lds_cap = pl->p.deterministic ? 150 * 1024 : 80 * 1024;
-  const size_t budget = col_lds + 1024 < lds_cap ? lds_cap - col_lds - 1024 : 0;
+  // Histograms: one per wavefront when the LDS of the resident blocks allows; else wavefronts take turns
+  // on a copy, so that the sums never depend on scheduling.
+  const int waves = (geo.threads + 63) / 64;
+  const size_t lds = 160 * 1024;
+  cc.thr_lds = geo.smem + sizeof(int) * (size_t)n_edges + sizeof(double) * (size_t)max_nv <= lds;
+  const size_t fixed = geo.smem + (cc.thr_lds ? sizeof(int) * (size_t)n_edges : 0) + 512;
+  const size_t budget = lds / geo.per_cu > fixed ? lds / geo.per_cu - fixed : 0;
   for (auto& gc : cc.groups) {
-    const int copies = (int)std::min<size_t>((size_t)waves, budget / (sizeof(double) * (size_t)std::max(1, gc.nv)));
-    gc.copies = std::max(1, copies);
-    if (pl->p.deterministic && gc.copies < waves) {
-      pl->err = "deterministic mode: one post-pass histogram per wavefront does not fit LDS for these bins";
-      throw Fail{PKM_ENOMEM};
+    const size_t row = sizeof(double) * (size_t)std::max(1, gc.nv);
+    const int copies = std::max(1, (int)std::min<size_t>((size_t)waves, budget / row));
+    gc.turns = (waves + copies - 1) / copies;
+    gc.copies = (waves + gc.turns - 1) / gc.turns;
+    if (pl->p.deterministic) {
+      const int w = ((n / pl->fs.e_post) * pl->fs.tile_post + 63) / 64;
+      const size_t left = col_lds + 1024 < 150 * 1024 ? 150 * 1024 - col_lds - 1024 : 0;
+      if (left / row < (size_t)w) {
+        pl->err = "deterministic mode: one post-pass histogram per wavefront does not fit LDS for these bins";
+        throw Fail{PKM_ENOMEM};
+      }
     }
   }
   cc.ell_max = ell_max;
@@ -739,33 +814,33 @@ template <typename T> void enqueue_compute(pkm_plan* pl) {
   const double off[3] = {pl->p.box_origin[0] - pl->p.observer[0], pl->p.box_origin[1] - pl->p.observer[1],
                          pl->p.box_origin[2] - pl->p.observer[2]};
   const double h = pl->p.box_len / n;
-  const double dc_scale = 2.0 / ((double)n * n * n);
+  const double dc_scale = 1.0 / ((double)n * n * n);
   for (size_t gi = 0; gi < cc.groups.size(); ++gi) {
     const GroupCfg& gc = cc.groups[gi];
-    const int* ft = pl->ftab_dev + 4 * gc.fofs;
-    const int* ftp = pl->ftab_dev + 4 * gc.pofs;
-    if (gc.nf > 0) {
+    if (gc.nf > 0 && cc.ntiles > 0) {
       {
         StageScope ss(pl, PKM_STAGE_ZPRE);
-        check_hip(pl, launch_zpre<T>(pl->fs, pl->g, dc_real ? (const T*)pl->d1 : nullptr, nullptr, pl->ptrs_dev,
-                                     gc.nf, ft, dc_scale, off, h, pl->ytab, pl->tw, pl->frame, cc.basis, s),
+        check_hip(pl, launch_zpre<T>(pl->fs, pl->g, dc_real ? (const T*)pl->d1 : nullptr, gc.nent,
+                                     pl->ftab_dev + gc.fofs, dc_scale, off, h, pl->ytab, pl->tw, pl->frame, cc.basis,
+                                     cc.kz_live, s),
                   "zpre");
       }
-      // kz-major fields: the column pass runs along x within each kz plane, the post-pass
-      // along the contiguous y lines
+      // the column pass runs along x within each kz plane, the post-pass along y
       StageScope ss(pl, PKM_STAGE_YCOL);
-      check_hip(pl, launch_col<T>(pl->fs, pl->ptrs_dev, gc.nf, 0, false, pl->tw, s, true), "field column pass");
+      check_hip(pl, launch_col_fields<T>(pl->fs, pl->ftab_dev + gc.fofs, gc.nent, cc.kz_live, cc.tmax, pl->tw, s),
+                "field column pass");
     }
-    int nblocks = 0;
     {
       StageScope ss(pl, PKM_STAGE_XPOST);
-      check_hip(pl, launch_xpost<T>(pl->fs, pl->ptrs_dev, gc.nf, ftp, gc.nslots, gi == 0 ? 1 : 0, pl->c, pl->ytab,
-                                    BinSpec{pl->thr_dev, cc.nb, gc.copies}, (double)(2.0 * M_PI / pl->p.box_len),
-                                    pl->partial, &nblocks, pl->tw, pl->frame, cc.basis, s),
+      check_hip(pl, launch_xpost<T>(pl->fs, gc.nf, pl->ftab_dev + gc.pofs, gc.nslots, gi == 0 ? 1 : 0,
+                                    pl->c, pl->ytab,
+                                    BinSpec{nullptr, pl->thr_dev, cc.nb, gc.copies, gc.turns, cc.thr_lds},
+                                    (double)(2.0 * M_PI / pl->p.box_len), pl->partial, cc.post_blocks, pl->tw,
+                                    pl->frame, cc.basis, pl->tiles_dev, cc.ntiles, s),
                 "post-pass");
     }
     StageScope ss(pl, PKM_STAGE_REDUCE);
-    check_hip(pl, launch_reduce(pl->partial, nblocks, gc.nv, pl->out_dev, pl->map_dev + gc.mofs, 1, s), "reduce");
+    check_hip(pl, launch_reduce(pl->partial, cc.post_blocks, gc.nv, pl->out_dev, pl->map_dev + gc.mofs, 1, s), "reduce");
   }
 }
 
@@ -891,7 +966,7 @@ void run_kmu(pkm_plan* pl, const double* k_edges, int nke, const double* mu_edge
     double l[3] = {pl->p.los[0], pl->p.los[1], pl->p.los[2]};
     const double ln = std::sqrt(l[0] * l[0] + l[1] * l[1] + l[2] * l[2]);
     for (double& v : l) v /= ln;
-    check_hip(pl, launch_kmu<T>(pl->fs, pl->c, l, BinSpec{thr_d, nb, 1}, mue_d, nmu, part, nblk, s), "kmu");
+    check_hip(pl, launch_kmu<T>(pl->fs, pl->c, l, BinSpec{thr_d, nullptr, nb, 1, 1, 0}, mue_d, nmu, part, nblk, s), "kmu");
     check_hip(pl, launch_reduce(part, nblk, nvals, outd, nullptr, 0, s), "reduce");
     std::vector<double> res(nvals);
     check_hip(pl, hipMemcpy(res.data(), outd, sizeof(double) * nvals, hipMemcpyDeviceToHost), "download");
@@ -977,7 +1052,7 @@ void run_kmu_noalloc(pkm_plan* pl, const double* k_edges, int nke, const double*
   for (double& v : l) v /= ln;
   // every block writes all 2 ncells of its partial row, the reduction and the normalisation
   // write every cell: nothing of an earlier call is read
-  check_hip(pl, launch_kmu<T>(pl->fs, pl->c, l, BinSpec{thr_d, nb, 1}, mue_d, nmu, part, KMU_NOALLOC_BLOCKS, s),
+  check_hip(pl, launch_kmu<T>(pl->fs, pl->c, l, BinSpec{thr_d, nullptr, nb, 1, 1, 0}, mue_d, nmu, part, KMU_NOALLOC_BLOCKS, s),
             "kmu");
   check_hip(pl, launch_reduce(part, KMU_NOALLOC_BLOCKS, 2 * ncells, sums, nullptr, 0, s), "reduce");
   check_hip(pl, launch_kmu_finish(sums, ncells, pl->norm_I, pl->shot, pk_d, nm_d, s), "kmu finish");
@@ -1000,11 +1075,8 @@ template <typename T> void run_fft_inverse(pkm_plan* pl, void* in, void* out) {
   void** sp = scratch_ptrs(pl, {in});
   check_hip(pl, launch_col<T>(pl->fs, sp, 1, 0, true, pl->tw, s), "x pass");
   check_hip(pl, launch_col<T>(pl->fs, sp, 1, 1, true, pl->tw, s), "y pass");
-  const double off[3] = {0, 0, 0};
   const int n = pl->p.nmesh;
-  check_hip(pl, launch_zpre<T>(pl->fs, in, nullptr, (T*)out, pl->ptrs_dev, 0, pl->ftab_dev, 2.0 / ((double)n * n * n),
-                               off, 1.0, pl->ytab, pl->tw, pl->frame, 0, s),
-            "z inverse");
+  check_hip(pl, launch_zinv<T>(pl->fs, in, (T*)out, 2.0 / ((double)n * n * n), pl->tw, s), "z inverse");
   check_hip(pl, hipStreamSynchronize(s), "sync");
 }
 
@@ -1015,10 +1087,8 @@ template <typename T> void read_dc(pkm_plan* pl, void* host, size_t bytes) {
     return;
   }
   void* tmp = dalloc(pl, pl->mesh_bytes);
-  const double off[3] = {0, 0, 0};
   const int n = pl->p.nmesh;
-  hipError_t e = launch_zpre<T>(pl->fs, pl->g, nullptr, (T*)tmp, pl->ptrs_dev, 0, pl->ftab_dev,
-                                2.0 / ((double)n * n * n), off, 1.0, pl->ytab, pl->tw, pl->frame, 0, s);
+  hipError_t e = launch_zinv<T>(pl->fs, pl->g, (T*)tmp, 2.0 / ((double)n * n * n), pl->tw, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e == hipSuccess) e = hipMemcpy(host, tmp, bytes, hipMemcpyDeviceToHost);
   dfree(pl, tmp);
@@ -1026,12 +1096,6 @@ template <typename T> void read_dc(pkm_plan* pl, void* host, size_t bytes) {
 }
 
 // Launch shape of the transform passes for one mesh size and precision.
-// Field buffers are kz-major, [kz][x][y], with kz planes of n n complex values plus 256
-// bytes (32 FP32 or 16 FP64 values): the column pass steps from row to row within a plane and
-// the pre-pass writes across planes; a plain power-of-two plane stride puts those accesses on
-// few HBM channels.
-int field_pad(bool fp64) { return fp64 ? 16 : 32; }
-
 bool make_shape(const pkm_params& p, FftShape* out) {
   FftShape fs{};
   const int n = p.nmesh;
@@ -1095,7 +1159,7 @@ bool make_shape(const pkm_params& p, FftShape* out) {
     if (next.zlines * pt_z > zmax || n % next.zlines || zpass_smem_bytes(next, fp64) > 160 * 1024) break;
     fs = next;
   }
-  fs.fpad = field_pad(fp64);
+  fs.col_builtin = true;
   *out = fs;
   return true;
 }
@@ -1115,6 +1179,7 @@ bool apply_shape(const pkm_params& p, const pkm_shape& sh, FftShape* fs, int* ts
   if (sh.tile) f.tile = sh.tile;
   if (f.tile < 1 || nh % f.tile || (n / f.e_col) * f.tile > 512 || colpass_smem_bytes(f, fp64) > 160 * 1024)
     return fail("column-pass tile breaks a kernel limit");
+  f.col_builtin = f.e_col == fs->e_col && f.tile == fs->tile;
   if (sh.e_z) {
     if (!is_elem(sh.e_z) || !make_sched(nh, sh.e_z, &f.sched_z, &f.nst_z)) return fail("bad e_z");
     f.e_z = sh.e_z;
@@ -1129,7 +1194,7 @@ bool apply_shape(const pkm_params& p, const pkm_shape& sh, FftShape* fs, int* ts
   }
   if (sh.tile_post) f.tile_post = sh.tile_post;
   if (f.tile_post < 1 || nh % f.tile_post || (n / f.e_post) * f.tile_post > 256 ||
-      xpost_base_bytes(f, fp64) > 150 * 1024)
+      bin_limit_base(f, fp64) > 150 * 1024)
     return fail("post-pass tile breaks a kernel limit");
   if (sh.post_axis && sh.post_axis != 2)
     return fail("post_axis must be 0 or 2: the post-pass runs along y over kz-major field buffers");
@@ -1209,7 +1274,7 @@ void free_all(pkm_plan* pl) {
                     (void*)pl->map_dev, pl->tw, pl->ytab, pl->invw, pl->phase, (void*)pl->thr_dev, (void*)pl->partial,
                     (void*)pl->out_dev, (void*)pl->sums_dev, (void*)pl->cat_dev, (void*)pl->tile_count,
                     (void*)pl->tile_off, (void*)pl->tile_of, (void*)pl->tile_rank, pl->payload,
-                    (void*)pl->scan_sums, (void*)pl->paint_ptrs, (void*)pl->det_acc, (void*)pl->det_scale})
+                    (void*)pl->scan_sums, (void*)pl->tiles_dev, (void*)pl->paint_ptrs, (void*)pl->det_acc, (void*)pl->det_scale})
     dfree(pl, ptr);
   if (pl->slot) (void)hipHostFree(pl->slot);
   if (pl->done) (void)hipEventDestroy(pl->done);
@@ -1361,9 +1426,11 @@ int64_t footprint(const pkm_params* p, int ell_max, int n_edges, int64_t n_parti
   if (p->max_group > 0) nf = std::min(nf, p->max_group);
   nf = std::max(nf, 1);
   const int64_t meshes = (p->interlaced ? 6 : 4) + nf;
-  const int64_t pads = (int64_t)nf * (n / 2) * fs.fpad * 2 * (p->precision == PKM_FP64 ? 8 : 4);
+  const int64_t pads = nf * ((int64_t)field_bytes(p->nmesh, p->precision == PKM_FP64) - mesh);
   const int64_t nb = std::max(1, n_edges - 1);
-  const int64_t partial = (int64_t)post_blocks(fs) * (3 + ell_max / 2) * nb * 8;
+  const PostGeometry geo = post_geometry_of(p->nmesh, p->precision == PKM_FP64);
+  const int tiles = p->nmesh * ((p->nmesh / 2 + geo.tp - 1) / geo.tp);
+  const int64_t partial = (int64_t)post_blocks_for(geo, 0, tiles) * (3 + ell_max / 2) * nb * 8;
   const int64_t ts = 8;
   const int64_t ntiles = (n / ts) * (n / ts) * (n / ts);
   const int64_t det = p->deterministic ? 8 * n * n * n * (p->interlaced ? 2 : 1) : 0;
@@ -1472,8 +1539,8 @@ pkm_status pkm_plan_create_shaped(const pkm_params* p, const pkm_device* dev, co
     int want = fields_for(pl->p.ell_max_hint);
     if (p->max_group > 0) want = std::min(want, p->max_group);
     ensure_fields(pl, std::max(want, 1));
-    pl->ftab_dev = (int*)dalloc(pl, sizeof(int) * 4 * 64);
-    pl->ftab_cap = 4 * 64;
+    pl->ftab_cap = 64;
+    pl->ftab_dev = (FieldRec*)dalloc(pl, sizeof(FieldRec) * pl->ftab_cap);
     pl->paint_ptrs = (void**)dalloc(pl, sizeof(void*) * 3);
     void* pp[3] = {pl->s1, pl->s2, pl->g};
     check_hip(pl, hipMemcpy(pl->paint_ptrs, pp, sizeof pp, hipMemcpyHostToDevice), "upload paint pointers");
@@ -1753,7 +1820,7 @@ pkm_status pkm_autotune(const pkm_params* p, const pkm_device* dev, int32_t ell_
         if ((nh / e) * zl > (p->precision == PKM_FP64 ? 256 : 512) || (nh / e) * zl < 64) continue;
         pkm_shape s2 = cur; s2.e_z = e; s2.zlines = zl; c.push_back(s2);
       }
-    tune(c, {PKM_STAGE_ZFWD, PKM_STAGE_ZPRE});
+    tune(c, {PKM_STAGE_ZFWD});
   }
   {
     std::vector<pkm_shape> c;
@@ -1763,15 +1830,6 @@ pkm_status pkm_autotune(const pkm_params* p, const pkm_device* dev, int32_t ell_
         pkm_shape s2 = cur; s2.e_col = e; s2.tile = tl; c.push_back(s2);
       }
     tune(c, {PKM_STAGE_YCOL, PKM_STAGE_XCOMBINE, PKM_STAGE_IYCOL});
-  }
-  {
-    std::vector<pkm_shape> c;
-    for (int e : {4, 8})
-      for (int tl : {1, 2, 4, 8, 16}) {
-        if ((n / e) * tl > 256 || (n / e) * tl < 64) continue;
-        pkm_shape s2 = cur; s2.e_post = e; s2.tile_post = tl; c.push_back(s2);
-      }
-    tune(c, {PKM_STAGE_YCOL, PKM_STAGE_XPOST});
   }
   double m[PKM_NSTAGES];
   double tuned = time_shape(cur, m);
