@@ -635,15 +635,4 @@ template <typename T> __device__ __forceinline__ void lds_atomic_add(T* p, T v) 
   __hip_atomic_fetch_add((LT*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Bin index of an integer squared wavenumber: largest i with thr[i] <= n2, if i < nb; else -1.
-__device__ __forceinline__ int kbin_of(long long n2, const long long* __restrict__ thr, int nb) {
-  if (n2 < thr[0] || n2 >= thr[nb]) return -1;
-  int lo = 0, hi = nb;  // thr[lo] <= n2 < thr[hi]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (thr[mid] <= n2) lo = mid; else hi = mid;
-  }
-  return lo;
-}
-
 }  // namespace pkm

@@ -139,50 +139,105 @@ __global__ void __launch_bounds__(RED_THREADS) k_reduce(const double* __restrict
 // ------------------------------------------------------------------------------------------
 // global line of sight (k, mu) binning of |C|^2
 // ------------------------------------------------------------------------------------------
+// A thread walks KMU_ROWS consecutive y at one (x, kz), its k and mu bins and their limits in registers: from
+// row to row a mode mostly stays in its cell, so the search, the exact mu and the two LDS atomics are needed
+// only where it leaves it, and lanes (consecutive kz, often one cell) meet less on an address; `copies` of the
+// histogram spread the lanes that still do.  One thread per mode with 64-bit index divisions, a search and
+// a division and square root each took 0.91 ms at 512^3 in FP32, 0.28 now (reading C alone takes 0.1).
+constexpr int KMU_ROWS = 32;
+// doubles between copies: 4 modulo the 32 of a row of LDS banks
+__host__ __device__ constexpr int kmu_pitch(int nvals) { return (nvals + 31) / 32 * 32 + 4; }
+
 template <typename T>
-__global__ void k_kmu(int n, const cx<T>* __restrict__ cin, double l0, double l1, double l2,
-                      const long long* __restrict__ thr, int nb, const double* __restrict__ mue, int nmu,
+__global__ void __launch_bounds__(256) k_kmu(int n, const cx<T>* __restrict__ cin, double l0, double l1, double l2,
+                      const long long* __restrict__ thr, int nb, const double* __restrict__ mue, int nmu, int copies,
                       double* __restrict__ partial) {
   extern __shared__ __align__(16) unsigned char smem[];
   double* hist = reinterpret_cast<double*>(smem);
-  const int nvals = 2 * nb * nmu;
-  hist_zero(hist, nvals);
+  const int nvals = 2 * nb * nmu, pitch = kmu_pitch(nvals);
+  // limits of k bin b in klim[b + 1], klim[b + 2] and of mu bin j in mlim[j + 1], mlim[j + 2], the ranges
+  // below (bin -1) and above the edges included; the last mu bin has no upper limit
+  double* mlim = hist + copies * pitch;
+  int* klim = reinterpret_cast<int*>(mlim + nmu + 2);
+  hist_zero(hist, copies * pitch);
+  for (int i = threadIdx.x; i < nb + 3; i += blockDim.x) {
+    const long long t = i == 0 ? INT_MIN : i == nb + 2 ? INT_MAX : thr[i - 1];
+    klim[i] = (int)(t < INT_MAX ? t : INT_MAX);
+  }
+  for (int i = threadIdx.x; i < nmu + 2; i += blockDim.x)
+    mlim[i] = i == 0 ? -__builtin_huge_val() : i == nmu + 1 ? __builtin_huge_val() : mue[i - 1];
   __syncthreads();
   const int nh = n >> 1;
-  const size_t total = (size_t)n * n * nh;
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
-    const int kz = (int)(i % nh);
-    const size_t xy = i / nh;
-    const int y = (int)(xy % n), x = (int)(xy / n);
-    if (x == nh || y == nh) continue;
-    const int fx = sfreq(x, n), fy = sfreq(y, n);
-    const long long n2 = (long long)fx * fx + (long long)fy * fy + (long long)kz * kz;
-    if (n2 == 0) continue;
-    const int kb = kbin_of(n2, thr, nb);
-    if (kb < 0) continue;
-    const double dot = __dadd_rn(__dadd_rn(__dmul_rn((double)fx, l0), __dmul_rn((double)fy, l1)),
-                                 __dmul_rn((double)kz, l2));
-    const double mu = __ddiv_rn(fabs(dot), __dsqrt_rn((double)n2));
-    // mu bin: last edge <= mu -> last bin; else largest j with mue[j] <= mu
-    int mb;
-    if (mu >= mue[nmu]) mb = nmu - 1;
-    else if (mu < mue[0]) mb = -1;
-    else {
-      int lo = 0, hi = nmu;
-      while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (mue[mid] <= mu) lo = mid; else hi = mid; }
-      mb = lo;
+  const int segs = (n + KMU_ROWS - 1) / KMU_ROWS;
+  const int items = n * segs * nh;
+  double* h = hist + (threadIdx.x & (copies - 1)) * pitch;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < items; i += gridDim.x * blockDim.x) {
+    const int kz = i % nh, xs = i / nh, x = xs / segs, y0 = (xs - x * segs) * KMU_ROWS;
+    if (x == nh) continue;
+    const int fx = sfreq(x, n), n2xz = fx * fx + kz * kz;
+    const double dx = __dmul_rn((double)fx, l0), dz = __dmul_rn((double)kz, l2);
+    const double omega = kz == 0 ? 1.0 : 2.0;
+    const cx<T>* c = cin + ((size_t)x * n + y0) * nh + kz;
+    // largest index whose limit is <= v, of limits [0] = -inf .. [top] = inf
+    auto find = [](const auto* lim, int top, auto v) {
+      int lo = 0;
+      while (top - lo > 1) { const int mid = (lo + top) >> 1; if (lim[mid] <= v) lo = mid; else top = mid; }
+      return lo;
+    };
+    const int f0 = sfreq(y0, n), s2 = n2xz + f0 * f0;
+    int kb = find(klim, nb + 2, s2) - 1, klo = klim[kb + 1], khi = klim[kb + 2];
+    int mb = find(mlim, nmu + 1, fabs(dx + (double)f0 * l1 + dz) * rsqrt((double)max(s2, 1))) - 1;
+    double mlo = mlim[mb + 1], mhi = mlim[mb + 2];
+    int count = 0;
+    double sum = 0.0;
+    auto put = [&]() {
+      if (count == 0) return;
+      double* q = h + 2 * (kb * nmu + mb);
+      lds_atomic_add<double>(q, omega * count);
+      lds_atomic_add<double>(q + 1, omega * sum);
+      count = 0;
+      sum = 0.0;
+    };
+    constexpr int CH = 8;  // rows loaded ahead
+    for (int r0 = 0; r0 < KMU_ROWS && y0 + r0 < n; r0 += CH) {
+      cx<T> v[CH];
+#pragma unroll
+      for (int r = 0; r < CH; ++r) v[r] = y0 + r0 + r < n ? gload<T>(c, (size_t)(r0 + r) * nh) : mk<T>(T(0), T(0));
+#pragma unroll
+      for (int r = 0; r < CH; ++r) {
+        const int y = y0 + r0 + r;
+        const int fy = sfreq(y, n), n2 = n2xz + fy * fy;
+        if (y >= n || y == nh || n2 == 0) continue;
+        const double dot = fabs(__dadd_rn(__dadd_rn(dx, __dmul_rn((double)fy, l1)), dz));
+        const double near = dot * rsqrt((double)n2);
+        if (n2 < klo || n2 >= khi || near < mlo + 1e-12 || near >= mhi - 1e-12) {
+          put();
+          while (n2 >= khi) { klo = khi; khi = klim[++kb + 2]; }
+          while (n2 < klo) { khi = klo; klo = klim[--kb + 1]; }
+          while (near >= mhi) { mlo = mhi; mhi = mlim[++mb + 2]; }
+          while (near < mlo) { mhi = mlo; mlo = mlim[--mb + 1]; }
+          // The exactly rounded mu decides; further from the limits than the error of the reciprocal root
+          // both give the same bin.
+          if (near < mlo + 1e-12 || near >= mhi - 1e-12) {
+            mb = find(mlim, nmu + 1, __ddiv_rn(dot, __dsqrt_rn((double)n2))) - 1;
+            mlo = mlim[mb + 1];
+            mhi = mlim[mb + 2];
+          }
+        }
+        if (kb >= 0 && kb < nb && mb >= 0) {
+          ++count;
+          sum += (double)v[r].x * (double)v[r].x + (double)v[r].y * (double)v[r].y;
+        }
+      }
     }
-    if (mb < 0) continue;
-    const cx<T> v = cin[i];
-    const double p2 = (double)v.x * (double)v.x + (double)v.y * (double)v.y;
-    const double omega = (kz == 0) ? 1.0 : 2.0;
-    const int cell = kb * nmu + mb;
-    lds_atomic_add<double>(&hist[2 * cell], omega);
-    lds_atomic_add<double>(&hist[2 * cell + 1], omega * p2);
+    put();
   }
   __syncthreads();
-  hist_flush(hist, 1, nvals, partial + (size_t)blockIdx.x * nvals);
+  for (int v = threadIdx.x; v < nvals; v += blockDim.x) {
+    double t = 0.0;
+    for (int k = 0; k < copies; ++k) t += hist[k * pitch + v];
+    partial[(size_t)blockIdx.x * nvals + v] = t;
+  }
 }
 
 // Normalisation of reduced (k, mu) sums on the device, FP64 with explicitly rounded
@@ -287,9 +342,12 @@ hipError_t launch_reduce(const double* partial, int nblocks, int nvals, double* 
 template <typename T>
 hipError_t launch_kmu(const FftShape& fs, const void* c_in, const double* los, const BinSpec& bs,
                       const double* mu_edges, int nmu, double* partial, int nblk, hipStream_t s) {
-  const size_t sm = sizeof(double) * 2 * (size_t)bs.nb * nmu;
+  const int pitch = kmu_pitch(2 * bs.nb * nmu);
+  int copies = 8;  // within 40 KB: four blocks a CU
+  while (copies > 1 && sizeof(double) * copies * (size_t)pitch > 40 * 1024) copies /= 2;
+  const size_t sm = sizeof(double) * ((size_t)copies * pitch + nmu + 2) + sizeof(int) * (size_t)(bs.nb + 3);
   k_kmu<T><<<nblk, 256, sm, s>>>(fs.n, (const cx<T>*)c_in, los[0], los[1], los[2], bs.thr, bs.nb, mu_edges, nmu,
-                                 partial);
+                                 copies, partial);
   return hipGetLastError();
 }
 
