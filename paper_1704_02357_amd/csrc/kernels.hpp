@@ -83,20 +83,24 @@ hipError_t launch_catalog_sums(const double* w, const double* nbar, int64_t n, d
 
 template <typename T> hipError_t launch_fill(T* p, size_t n, T v, hipStream_t s);
 
-// Counting sort of particles by tile of their base node (tile side ts): per particle the
-// tile id and its rank within the tile (atomic counter), for catalog entries [base, base+n).
-// `count` holds TILE_COUNT_COPIES zeroed copies of ntiles + 1 counters (a block uses one copy);
-// launch_tile_offsets turns them in place into per-copy start offsets.
-hipError_t launch_tile_sort(const double* pos, int64_t n, int64_t base, const double* origin, double scale,
-                            int nmesh, int ts, int* count, int* tile_of, int* rank, hipStream_t s);
-// Exclusive scan of the tile counts (off has ntiles + 1 entries), then the particle payload
-// (x, y, z, w for data / -alpha w for randoms; 32 bytes each) written in tile order.
-hipError_t launch_tile_offsets(int* count, int ntiles, int* off, const int* tile_of, const int* rank,
-                               int64_t nd, int64_t ntot, const double* dpos, const double* dw, const double* rpos,
-                               const double* rw, double alpha, void* payload, int* bsum, hipStream_t s);
+// How the particles are sorted by the tile of their base node.  The counters are `rows` rows of `pitch`: with
+// chunk > 0 one row per chunk of that many particles, counted in LDS; else TILE_COUNT_COPIES rows of global
+// counters (a block uses one row), zeroed by the caller.  keys: tiles, or groups of the tiles one painting
+// block takes; per: entries of the offsets a painting block spans.
+struct TileSort {
+  int keys, per, chunk, rows, pitch;
+};
+// scratch_bytes: what the rows of a chunked sort may take.
+TileSort tile_sort_of(int nmesh, int ts, int ntiles, int64_t ntot, bool det, size_t scratch_bytes);
+// The sort: per particle its key and rank, the offsets (keys + 1 entries) and the payload (x, y, z, w for
+// data / -alpha w for randoms; 32 bytes each) in key order.  count: the rows (turned into start offsets).
+hipError_t launch_tile_sort(const TileSort& t, const double* origin, double scale, int nmesh, int ts, int64_t nd,
+                            int64_t nr, const double* dpos, const double* dw, const double* rpos, const double* rw,
+                            double alpha, int* count, int* tile_of, int* rank, int* off, int* bsum, void* payload,
+                            hipStream_t s);
 constexpr int TILE_COUNT_COPIES = 8;
 // Scratch entries needed by the tile scan (block sums).
-inline int tile_scan_scratch(int ntiles) { return (ntiles + 1023) / 1024 + 1; }
+inline int tile_scan_scratch(int ntiles) { return (ntiles + 255) / 256 + 1; }
 // Tile-wise painting from the sorted payload.
 template <typename T>
 // wmax_d / wmax_r: device pointers to the largest |w| of each catalog (wmax_r null without
@@ -104,7 +108,7 @@ template <typename T>
 // acc (deterministic mode, else null): 64-bit accumulators, n^3 per mesh (two meshes when d2 is
 // set), zeroed by the caller; the paint then leaves d1 / d2 untouched and writes the shared
 // fixed-point scale to *gsc, and launch_det_convert turns the accumulators into the meshes.
-hipError_t launch_paint_tiles(const int* off, const void* payload, int ntiles, const double* origin, double scale,
+hipError_t launch_paint_tiles(const int* off, int per, const void* payload, int ntiles, const double* origin, double scale,
                               int nmesh, int window, int ts, T* d1, T* d2, const double* wmax_d,
                               const double* wmax_r, double alpha, hipStream_t s, unsigned long long* acc = nullptr,
                               double* gsc = nullptr);

@@ -176,13 +176,60 @@ __global__ void k_tile_count(const double* __restrict__ pos, int64_t n, int64_t 
   }
 }
 
-constexpr int SCAN_THREADS = 1024;
+// Counting in LDS.  Atomics on global counters are done at the memory side, about 23 a nanosecond, which bound
+// k_tile_count for random catalogs.  Here a block counts one contiguous chunk of the catalogs into counters of
+// 16 bits that all fit in its LDS (a chunk has fewer than 2^16 particles) and writes them out as a row; the
+// scan turns the rows into each chunk's start in every tile.  Keys are the tiles, or the groups of tiles that
+// one painting block takes.  21 million random particles at 512^3: 0.85 to 0.91 ms with global counters, 0.20 with
+// these, and 0.06 more in the scan of the longer rows.
+__global__ void __launch_bounds__(1024)
+    k_tile_count_lds(const double* __restrict__ dpos, const double* __restrict__ rpos, int64_t nd, int64_t ntot,
+                     int chunk, double o0, double o1, double o2, double scale, int nmesh, int ts_log2, int zt_log2,
+                     int nkeys, int pitch, int* __restrict__ rows, int* __restrict__ key_of, int* __restrict__ rank) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  unsigned* cnt = reinterpret_cast<unsigned*>(smem);
+  const int words = (nkeys + 1) / 2;
+  for (int i = threadIdx.x; i < words; i += blockDim.x) cnt[i] = 0;
+  __syncthreads();
+  const int tpa = nmesh >> ts_log2;
+  const int64_t first = (int64_t)blockIdx.x * chunk;
+  const int64_t last = first + chunk < ntot ? first + chunk : ntot;
+  for (int64_t i0 = first + threadIdx.x; i0 < last; i0 += (int64_t)blockDim.x * CPT) {
+    double p[CPT][3];
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) {
+      const int64_t i = i0 + (int64_t)j * blockDim.x < last ? i0 + (int64_t)j * blockDim.x : i0;
+      const double* q = i < nd ? dpos + 3 * i : rpos + 3 * (i - nd);
+      p[j][0] = q[0];
+      p[j][1] = q[1];
+      p[j][2] = q[2];
+    }
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) {
+      const int64_t i = i0 + (int64_t)j * blockDim.x;
+      if (i >= last) break;
+      double u[3];
+      mesh_u(p[j], 0, o0, o1, o2, scale, u);
+      int tc[3];
+      for (int a = 0; a < 3; ++a) tc[a] = wrap_floor(u[a], nmesh) >> ts_log2;
+      const int key = (tc[0] * tpa + tc[1]) * (tpa >> zt_log2) + (tc[2] >> zt_log2);
+      const int sh = 16 * (key & 1);
+      key_of[i] = key;
+      rank[i] = (int)(atomicAdd(&cnt[key >> 1], 1u << sh) >> sh & 0xffff);
+    }
+  }
+  __syncthreads();
+  int2* row = reinterpret_cast<int2*>(rows + (size_t)blockIdx.x * pitch);  // (pitch is even)
+  for (int i = threadIdx.x; i < words; i += blockDim.x) row[i] = make_int2(cnt[i] & 0xffff, cnt[i] >> 16);
+}
+
+constexpr int SCAN_THREADS = 256, SUMS_THREADS = 1024;
 // Exclusive scan in three launches: per-block scans (block sums out), one-block scan of
 // the block sums, and the addition of the scanned sums.  Coalesced throughout.
-__device__ __forceinline__ int block_scan_excl(int v, int* part) {
+template <int NT> __device__ __forceinline__ int block_scan_excl(int v, int* part) {
   part[threadIdx.x] = v;
   __syncthreads();
-  for (int d = 1; d < SCAN_THREADS; d <<= 1) {
+  for (int d = 1; d < NT; d <<= 1) {
     const int add = (int)threadIdx.x >= d ? part[threadIdx.x - d] : 0;
     __syncthreads();
     part[threadIdx.x] += add;
@@ -191,65 +238,75 @@ __device__ __forceinline__ int block_scan_excl(int v, int* part) {
   return part[threadIdx.x] - v;
 }
 
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_blocks(const int* __restrict__ count, int n,
+// Counters are `rows` rows of `pitch`; 32 rows are read at once, as the pass is bound by latency.
+constexpr int SCAN_ROWS = 32;
+__global__ void __launch_bounds__(SCAN_THREADS) k_scan_blocks(const int* __restrict__ count, int n, int rows, int pitch,
                                                               int* __restrict__ off, int* __restrict__ bsum) {
   __shared__ int part[SCAN_THREADS];
   const int i = blockIdx.x * SCAN_THREADS + threadIdx.x;
   int v = 0;
   if (i < n)
-    for (int c = 0; c < NCOPY; ++c) v += count[(size_t)c * (n + 1) + i];
-  const int ex = block_scan_excl(v, part);
+    for (int c0 = 0; c0 < rows; c0 += SCAN_ROWS) {
+#pragma unroll
+      for (int c = 0; c < SCAN_ROWS; ++c) v += c0 + c < rows ? count[(size_t)(c0 + c) * pitch + i] : 0;
+    }
+  const int ex = block_scan_excl<SCAN_THREADS>(v, part);
   if (i < n) off[i] = ex;
   if (threadIdx.x == SCAN_THREADS - 1) bsum[blockIdx.x] = ex + v;
 }
 
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_sums(int* __restrict__ bsum, int nb, int* __restrict__ off,
+__global__ void __launch_bounds__(SUMS_THREADS) k_scan_sums(int* __restrict__ bsum, int nb, int* __restrict__ off,
                                                             int n) {
-  __shared__ int part[SCAN_THREADS];
+  __shared__ int part[SUMS_THREADS];
   __shared__ int carry;
   if (threadIdx.x == 0) carry = 0;
   __syncthreads();
-  for (int base = 0; base < nb; base += SCAN_THREADS) {
+  for (int base = 0; base < nb; base += SUMS_THREADS) {
     const int i = base + threadIdx.x;
     const int v = i < nb ? bsum[i] : 0;
-    const int ex = block_scan_excl(v, part);
+    const int ex = block_scan_excl<SUMS_THREADS>(v, part);
     if (i < nb) bsum[i] = carry + ex;
     __syncthreads();
-    if (threadIdx.x == SCAN_THREADS - 1) carry += ex + v;
+    if (threadIdx.x == SUMS_THREADS - 1) carry += ex + v;
     __syncthreads();
   }
   if (threadIdx.x == 0) off[n] = carry;
 }
 
-// Final tile offsets, and the counters turned in place into per-copy start offsets:
+// Final tile offsets, and the counters turned in place into per-row start offsets:
 // count[c][i] <- off[i] + sum over c' < c of count[c'][i].
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_add(const int* __restrict__ bsum, int n,
+__global__ void __launch_bounds__(SCAN_THREADS) k_scan_add(const int* __restrict__ bsum, int n, int rows, int pitch,
                                                            int* __restrict__ off, int* __restrict__ count) {
   const int i = blockIdx.x * SCAN_THREADS + threadIdx.x;
   if (i >= n) return;
   int start = off[i] + bsum[blockIdx.x];
   off[i] = start;
-  for (int c = 0; c < NCOPY; ++c) {
-    int* p = count + (size_t)c * (n + 1) + i;
-    const int v = *p;
-    *p = start;
-    start += v;
+  for (int c0 = 0; c0 < rows; c0 += SCAN_ROWS) {
+    int v[SCAN_ROWS];
+#pragma unroll
+    for (int c = 0; c < SCAN_ROWS; ++c) v[c] = c0 + c < rows ? count[(size_t)(c0 + c) * pitch + i] : 0;
+#pragma unroll
+    for (int c = 0; c < SCAN_ROWS; ++c) {
+      if (c0 + c < rows) count[(size_t)(c0 + c) * pitch + i] = start;
+      start += v[c];
+    }
   }
 }
 
-// Scatter each particle's payload (x, y, z, signed weight) to its slot in tile order.
+// Scatter each particle's payload (x, y, z, signed weight) to its slot in tile order.  The row of a
+// particle's counter is its chunk (chunk > 0) or the copy in the top bits of its rank.
 __global__ void k_tile_scatter(const int* __restrict__ tile_of, const int* __restrict__ rank, int64_t nd, int64_t n,
-                               int ntiles, const int* __restrict__ start, const double* __restrict__ dpos,
+                               int pitch, int chunk, const int* __restrict__ start, const double* __restrict__ dpos,
                                const double* __restrict__ dw, const double* __restrict__ rpos,
                                const double* __restrict__ rw, double alpha, double4* __restrict__ payload) {
   // CPT particles per thread and round, loads first: several offset lookups in flight at once
   const int64_t stride = (int64_t)gridDim.x * blockDim.x * CPT;
-  for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x * CPT + threadIdx.x; i0 < n; i0 += stride) {
+  for (int64_t b0 = (int64_t)blockIdx.x * blockDim.x * CPT; b0 < n; b0 += stride) {
     int dst[CPT];
     double4 p[CPT];
 #pragma unroll
     for (int j = 0; j < CPT; ++j) {
-      const int64_t i = i0 + (int64_t)j * blockDim.x;
+      const int64_t i = b0 + threadIdx.x + (int64_t)j * blockDim.x;
       dst[j] = -1;
       if (i < n) {
         const bool isd = i < nd;
@@ -261,8 +318,8 @@ __global__ void k_tile_scatter(const int* __restrict__ tile_of, const int* __res
         p[j].z = pos[3 * k + 2];
         p[j].w = (wp ? wp[k] : 1.0) * (isd ? 1.0 : -alpha);
         const int r = rank[i];
-        const int copy = (int)((unsigned)r >> RANK_BITS);
-        dst[j] = start[(size_t)copy * (ntiles + 1) + tile_of[i]] + (r & ((1 << RANK_BITS) - 1));
+        const int row = chunk > 0 ? (int)((unsigned)i / (unsigned)chunk) : (int)((unsigned)r >> RANK_BITS);
+        dst[j] = start[(size_t)row * pitch + tile_of[i]] + (r & ((1 << RANK_BITS) - 1));
       }
     }
 #pragma unroll
@@ -423,7 +480,7 @@ template <int W, int TS, int ZT> struct PaintShape {
 // integer atomics at the shared scale *gsc, instead of floating-point atomics to d1 / d2.
 template <typename T, int W, int TS, int ZT, bool DET>
 __global__ void __launch_bounds__((PaintShape<W, TS, ZT>::THREADS))
-    k_paint_tiles(const int* __restrict__ off, const double4* __restrict__ payload, double o0, double o1, double o2,
+    k_paint_tiles(const int* __restrict__ off, int per, const double4* __restrict__ payload, double o0, double o1, double o2,
                   double scale, int nmesh, T* __restrict__ d1, T* __restrict__ d2, const double* __restrict__ wmax_d,
                   const double* __restrict__ wmax_r, double alpha, unsigned long long* __restrict__ acc1,
                   unsigned long long* __restrict__ acc2, const double* __restrict__ gsc) {
@@ -438,10 +495,9 @@ __global__ void __launch_bounds__((PaintShape<W, TS, ZT>::THREADS))
   // is a fixed range of z, and a survey that fills part of the box loads some XCDs twice as much as others.
   const int row = blockIdx.x / (tpa / ZT);
   const int tile = (row * (tpa / ZT) + (blockIdx.x + row) % (tpa / ZT)) * ZT;
-  int at[ZT + 1];
-#pragma unroll
-  for (int k = 0; k <= ZT; ++k) at[k] = off[tile + k];
-  const int start = at[0], end = at[ZT];
+  // `off` has an entry per tile (per = ZT of them a block) or per block (per = 1)
+  const int* at = off + tile / ZT * per;
+  const int start = at[0], end = at[per];
   if (start == end) return;
   double* r1 = reinterpret_cast<double*>(smem);   // FP64 accumulation for both precisions
   const bool two = d2 != nullptr;
@@ -451,15 +507,14 @@ __global__ void __launch_bounds__((PaintShape<W, TS, ZT>::THREADS))
   const int tz = tile % tpa, ty = (tile / tpa) % tpa, tx = tile / (tpa * tpa);
   const int t0[3] = {tx * ts, ty * ts, tz * ts};
   // fixed-point scale (FP32 meshes): no region cell can exceed B = (particles that reach it: those of
-  // two neighbouring tiles of the row) x (largest |payload weight|), since a particle's taps sum to its
+  // two neighbouring tiles of the row, at most) x (largest |payload weight|), since a particle's taps sum to its
   // weight; B sc <= 2^61
   double sc = 1.0;
   if constexpr (DET) {
     sc = *gsc;
   } else if constexpr (sizeof(T) == 4) {
-    int most = at[1] - at[0];
-#pragma unroll
-    for (int k = 2; k <= ZT; ++k) most = max(most, at[k] - at[k - 2]);
+    int most = at[1] - start;
+    for (int k = 2; k <= per; ++k) most = max(most, at[k] - at[k - 2]);
     const double wm = fmax(*wmax_d, wmax_r ? alpha * *wmax_r : 0.0);
     const double bound = (double)most * wm;
     int e = 0;
@@ -471,11 +526,11 @@ __global__ void __launch_bounds__((PaintShape<W, TS, ZT>::THREADS))
   // A unit of work is one particle on one mesh, or, where that leaves most of the block idle, one slab of
   // its taps (slabs everywhere repeat the weights and cost a dense survey 1.07 -> 1.68 ms).
   const bool fine = (end - start) < (int)blockDim.x / 2;
-  const int per = (two ? 2 : 1) * (fine ? W : 1);
-  const int units = (end - start) * per;
+  const int parts = (two ? 2 : 1) * (fine ? W : 1);
+  const int units = (end - start) * parts;
   for (int j = threadIdx.x; j < units; j += blockDim.x) {
     const int q = fine ? (two ? j / (2 * W) : j / W) : (two ? j / 2 : j);
-    const int sub = j - q * per;
+    const int sub = j - q * parts;
     const bool second = fine ? sub >= W : sub == 1;
     const int a0 = fine ? (second ? sub - W : sub) : 0;
     const double4 p = payload[start + q];
@@ -570,35 +625,75 @@ template <typename T> hipError_t launch_fill(T* p, size_t n, T v, hipStream_t s)
   return hipGetLastError();
 }
 
-hipError_t launch_tile_sort(const double* pos, int64_t n, int64_t base, const double* origin, double scale,
-                            int nmesh, int ts, int* count, int* tile_of, int* rank, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  int64_t blocks = (n + 256 * CPT - 1) / (256 * CPT);
-  if (blocks > 16384) blocks = 16384;
+int paint_tiles_per_block(int nmesh, int ts, int ntiles) {
+  // More tiles a block (8-node tiles) mean fewer halo cells and fewer, longer rows of atomics, which the memory
+  // side takes at about 20 a nanosecond whatever their length (512^3, 2 million uniform particles: 1.30, 1.10,
+  // 1.01 ms for 1, 2, 4); fewer mean more blocks to spread a survey's dense part over (128^3 mock 52, 71,
+  // 66 us; 256^3 survey 213, 175, 240 us; 512^3 0.80, 0.82, 0.76 ms).
   const int tpa = nmesh / ts;
-  k_tile_count<<<(unsigned)blocks, 256, 0, s>>>(pos, n, base, origin[0], origin[1], origin[2], scale, nmesh,
-                                                __builtin_ctz(ts), tpa * tpa * tpa, count, tile_of, rank);
-  return hipGetLastError();
+  if (ts != 8) return 1;
+  if (ntiles >= 1 << 18 && tpa % 4 == 0) return 4;
+  return ntiles >= 1 << 15 && tpa % 2 == 0 ? 2 : 1;
 }
 
-hipError_t launch_tile_offsets(int* count, int ntiles, int* off, const int* tile_of, const int* rank,
-                               int64_t nd, int64_t ntot, const double* dpos, const double* dw, const double* rpos,
-                               const double* rw, double alpha, void* payload, int* bsum, hipStream_t s) {
-  const int nblk = (ntiles + SCAN_THREADS - 1) / SCAN_THREADS;
-  k_scan_blocks<<<nblk, SCAN_THREADS, 0, s>>>(count, ntiles, off, bsum);
-  k_scan_sums<<<1, SCAN_THREADS, 0, s>>>(bsum, nblk, off, ntiles);
-  k_scan_add<<<nblk, SCAN_THREADS, 0, s>>>(bsum, ntiles, off, count);
+TileSort tile_sort_of(int nmesh, int ts, int ntiles, int64_t ntot, bool det, size_t scratch_bytes) {
+  // Counters in LDS where they fit: one per tile, or, on larger meshes, one per painting block (not in the
+  // deterministic mode, whose scale goes by the tiles).  256 chunks, one for each CU, or a multiple of that
+  // below 2^16 particles; no fewer particles than a quarter of the counters, whose rows the scan and the scatter
+  // read again (2 million particles at 512^3, 65536 counters, 123 chunks: count and scans 98 + 16 -> 36 + 27 us).
+  constexpr int KEYS = 72 * 1024, CHUNK = (1 << 16) - 1;
+  const int zt = paint_tiles_per_block(nmesh, ts, ntiles);
+  TileSort t{ntiles, zt, 0, TILE_COUNT_COPIES, ntiles + 1};
+  const bool group = ntiles > KEYS && !det;
+  const int keys = group ? ntiles / zt : ntiles;
+  if (keys > KEYS) return t;
+  const int64_t waves = (ntot + 256 * (int64_t)CHUNK - 1) / (256 * (int64_t)CHUNK);
+  const int64_t chunk = std::min<int64_t>(std::max<int64_t>({(ntot + 256 * waves - 1) / (256 * std::max<int64_t>(waves, 1)),
+                                                             keys / 4, 2048}), CHUNK);
+  const int64_t rows = (ntot + chunk - 1) / chunk;
+  const int pitch = (keys + 2) & ~1;
+  if (rows * (int64_t)pitch * 4 > (int64_t)scratch_bytes) return t;
+  return TileSort{keys, group ? 1 : zt, (int)chunk, (int)rows, pitch};
+}
+
+hipError_t launch_tile_sort(const TileSort& t, const double* origin, double scale, int nmesh, int ts, int64_t nd,
+                            int64_t nr, const double* dpos, const double* dw, const double* rpos, const double* rw,
+                            double alpha, int* count, int* tile_of, int* rank, int* off, int* bsum, void* payload,
+                            hipStream_t s) {
+  const int64_t ntot = nd + nr;
+  const int tpa = nmesh / ts;
+  if (t.chunk > 0) {
+    const int zt = (int)((int64_t)tpa * tpa * tpa / t.keys);
+    if (t.rows > 0)
+      k_tile_count_lds<<<t.rows, 1024, sizeof(unsigned) * ((t.keys + 1) / 2), s>>>(
+          dpos, rpos, nd, ntot, t.chunk, origin[0], origin[1], origin[2], scale, nmesh, __builtin_ctz(ts),
+          __builtin_ctz(zt), t.keys, t.pitch, count, tile_of, rank);
+  } else {
+    auto run = [&](const double* pos, int64_t n, int64_t base) {
+      if (n <= 0) return;
+      const int64_t blocks = std::min<int64_t>((n + 256 * CPT - 1) / (256 * CPT), 16384);
+      k_tile_count<<<(unsigned)blocks, 256, 0, s>>>(pos, n, base, origin[0], origin[1], origin[2], scale, nmesh,
+                                                    __builtin_ctz(ts), t.keys, count, tile_of, rank);
+    };
+    run(dpos, nd, 0);
+    run(rpos, nr, nd);
+  }
   hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int nblk = (t.keys + SCAN_THREADS - 1) / SCAN_THREADS;
+  k_scan_blocks<<<nblk, SCAN_THREADS, 0, s>>>(count, t.keys, t.rows, t.pitch, off, bsum);
+  k_scan_sums<<<1, SUMS_THREADS, 0, s>>>(bsum, nblk, off, t.keys);
+  k_scan_add<<<nblk, SCAN_THREADS, 0, s>>>(bsum, t.keys, t.rows, t.pitch, off, count);
+  e = hipGetLastError();
   if (e != hipSuccess || ntot == 0) return e;
-  int64_t blocks = (ntot + 256 * CPT - 1) / (256 * CPT);
-  if (blocks > 16384) blocks = 16384;
-  k_tile_scatter<<<(unsigned)blocks, 256, 0, s>>>(tile_of, rank, nd, ntot, ntiles, count, dpos, dw, rpos, rw,
+  const int64_t blocks = std::min<int64_t>((ntot + 256 * CPT - 1) / (256 * CPT), 16384);
+  k_tile_scatter<<<(unsigned)blocks, 256, 0, s>>>(tile_of, rank, nd, ntot, t.pitch, t.chunk, count, dpos, dw, rpos, rw,
                                                   alpha, (double4*)payload);
   return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_paint_tiles(const int* off, const void* payload, int ntiles, const double* origin, double scale,
+hipError_t launch_paint_tiles(const int* off, int per, const void* payload, int ntiles, const double* origin, double scale,
                               int nmesh, int window, int ts, T* d1, T* d2, const double* wmax_d,
                               const double* wmax_r, double alpha, hipStream_t s, unsigned long long* acc,
                               double* gsc) {
@@ -610,26 +705,22 @@ hipError_t launch_paint_tiles(const int* off, const void* payload, int ntiles, c
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  const int tpa = nmesh / ts;
+  const int zt = paint_tiles_per_block(nmesh, ts, ntiles);
 #define PKM_PAINT(WV, TV, ZV)                                                                                  \
-  if (window == WV && ts == TV && tpa % ZV == 0) {                                                             \
+  if (window == WV && ts == TV && zt == ZV) {                                                             \
     using S = PaintShape<WV, TV, ZV>;                                                                          \
     const size_t sm = sizeof(double) * ((S::CELLS1 + (two ? S::CELLS2 : 0) + 1) & ~1);                         \
     if (acc)                                                                                                   \
       k_paint_tiles<T, WV, TV, ZV, true><<<ntiles / ZV, S::THREADS, sm, s>>>(                                  \
-          off, pl, origin[0], origin[1], origin[2], scale, nmesh, d1, d2, wmax_d, wmax_r, alpha, acc, acc2, gsc); \
+          off, per, pl, origin[0], origin[1], origin[2], scale, nmesh, d1, d2, wmax_d, wmax_r, alpha, acc, acc2, gsc); \
     else                                                                                                       \
       k_paint_tiles<T, WV, TV, ZV, false><<<ntiles / ZV, S::THREADS, sm, s>>>(                                 \
-          off, pl, origin[0], origin[1], origin[2], scale, nmesh, d1, d2, wmax_d, wmax_r, alpha, nullptr, nullptr, \
+          off, per, pl, origin[0], origin[1], origin[2], scale, nmesh, d1, d2, wmax_d, wmax_r, alpha, nullptr, nullptr, \
           nullptr);                                                                                            \
     return hipGetLastError();                                                                                  \
   }
-  // Tiles per block (8-node tiles).  More of them mean fewer halo cells and fewer, longer rows of atomics,
-  // which the memory side takes at about 20 a nanosecond whatever their length (512^3, 2 million uniform
-  // particles: 1.30, 1.10, 1.01 ms for 1, 2, 4); fewer mean more blocks to spread a survey's dense part over
-  // (128^3 mock 52, 71, 66 us; 256^3 survey 213, 175, 240 us; 512^3 0.80, 0.82, 0.76 ms).
-  if (ntiles >= 1 << 18) { PKM_PAINT(1, 8, 4) PKM_PAINT(2, 8, 4) PKM_PAINT(3, 8, 4) }
-  if (ntiles >= 1 << 15) { PKM_PAINT(1, 8, 2) PKM_PAINT(2, 8, 2) PKM_PAINT(3, 8, 2) }
+  PKM_PAINT(1, 8, 4) PKM_PAINT(2, 8, 4) PKM_PAINT(3, 8, 4)
+  PKM_PAINT(1, 8, 2) PKM_PAINT(2, 8, 2) PKM_PAINT(3, 8, 2)
   PKM_PAINT(1, 8, 1) PKM_PAINT(2, 8, 1) PKM_PAINT(3, 8, 1)
   PKM_PAINT(1, 4, 1) PKM_PAINT(2, 4, 1) PKM_PAINT(3, 4, 1)
   PKM_PAINT(1, 16, 1) PKM_PAINT(2, 16, 1) PKM_PAINT(3, 16, 1)
@@ -647,10 +738,10 @@ hipError_t launch_det_convert(const unsigned long long* acc, T* d1, T* d2, int n
   return hipGetLastError();
 }
 
-template hipError_t launch_paint_tiles<float>(const int*, const void*, int, const double*, double, int, int, int,
+template hipError_t launch_paint_tiles<float>(const int*, int, const void*, int, const double*, double, int, int, int,
                                               float*, float*, const double*, const double*, double, hipStream_t,
                                               unsigned long long*, double*);
-template hipError_t launch_paint_tiles<double>(const int*, const void*, int, const double*, double, int, int, int,
+template hipError_t launch_paint_tiles<double>(const int*, int, const void*, int, const double*, double, int, int, int,
                                                double*, double*, const double*, const double*, double, hipStream_t,
                                                unsigned long long*, double*);
 template hipError_t launch_det_convert<float>(const unsigned long long*, float*, float*, int, const double*,

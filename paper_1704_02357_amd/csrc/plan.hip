@@ -525,9 +525,12 @@ template <typename T> void enqueue_paint(pkm_plan* pl, const DevCats& dc) {
   }
   const double alpha = alpha_of(dc.nd, dc.nr);
   const bool det = pl->p.deterministic != 0;
+  // (the rows of a chunked sort lie in s1, which the forward z pass writes after the paint)
+  const TileSort ts = tile_sort_of(n, pl->ts, pl->ntiles, ntot, det, pl->mesh_bytes);
   {
     StageScope ss(pl, PKM_STAGE_FILL);
-    check_hip(pl, launch_fill<int>(pl->tile_count, (size_t)TILE_COUNT_COPIES * (pl->ntiles + 1), 0, s), "fill");
+    if (ts.chunk == 0)
+      check_hip(pl, launch_fill<int>(pl->tile_count, (size_t)TILE_COUNT_COPIES * (pl->ntiles + 1), 0, s), "fill");
     if (det) {
       check_hip(pl, launch_fill<unsigned long long>(pl->det_acc, cells * (d2 ? 2 : 1), 0ull, s), "fill");
     } else {
@@ -537,17 +540,11 @@ template <typename T> void enqueue_paint(pkm_plan* pl, const DevCats& dc) {
   }
   {
     StageScope ss(pl, PKM_STAGE_PAINT);
-    check_hip(pl, launch_tile_sort(dc.dp, dc.nd, 0, pl->p.box_origin, scale, n, pl->ts, pl->tile_count, pl->tile_of,
-                                   pl->tile_rank, s),
+    check_hip(pl, launch_tile_sort(ts, pl->p.box_origin, scale, n, pl->ts, dc.nd, has_r ? dc.nr : 0, dc.dp, dc.dw, dc.rp,
+                                   dc.rw, alpha, ts.chunk > 0 ? (int*)pl->s1 : pl->tile_count, pl->tile_of,
+                                   pl->tile_rank, pl->tile_off, pl->scan_sums, pl->payload, s),
               "tile sort");
-    if (has_r)
-      check_hip(pl, launch_tile_sort(dc.rp, dc.nr, dc.nd, pl->p.box_origin, scale, n, pl->ts, pl->tile_count,
-                                     pl->tile_of, pl->tile_rank, s),
-                "tile sort");
-    check_hip(pl, launch_tile_offsets(pl->tile_count, pl->ntiles, pl->tile_off, pl->tile_of, pl->tile_rank, dc.nd,
-                                      ntot, dc.dp, dc.dw, dc.rp, dc.rw, alpha, pl->payload, pl->scan_sums, s),
-              "tile offsets");
-    check_hip(pl, launch_paint_tiles<T>(pl->tile_off, pl->payload, pl->ntiles, pl->p.box_origin, scale, n,
+    check_hip(pl, launch_paint_tiles<T>(pl->tile_off, ts.per, pl->payload, pl->ntiles, pl->p.box_origin, scale, n,
                                         pl->p.window, pl->ts, d1, d2, pl->sums_dev + 4,
                                         has_r ? pl->sums_dev + 5 : nullptr, alpha, s,
                                         det ? pl->det_acc : nullptr, det ? pl->det_scale : nullptr),
