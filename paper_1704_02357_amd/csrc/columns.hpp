@@ -67,7 +67,8 @@ __global__ void __launch_bounds__((NC > 0 ? (NC / E) * TC : XMAX_THREADS)) k_col
 // both tiles are loaded, combined, transformed, and the buffers hold one field each from here on.
 // Rows whose modes all lie at or beyond the last k edge (fx^2 + kz^2 >= tmax) belong to no bin and are
 // not written: 21% of the bytes with edges up to the Nyquist wavenumber.
-// Bound by memory: 512^3, 14 fields: 2.79 ms, 5.0 TB/s (a pass over the fields alone 2.75 ms before, all modes);
+// Bound by memory: 512^3, 14 fields: 2.69 ms, 5.3 TB/s (2.75 ms before for every mode; 2.79 with 64-bit addresses
+// per row, of which 14 registers a thread spilled: 30% more written);
 // 432^3, 15 fields 2.85 -> 1.89 ms; 128^3, 289 fields 460 -> 411..455 us.
 // ------------------------------------------------------------------------------------------
 template <typename T, int N>
@@ -83,23 +84,25 @@ __global__ void __launch_bounds__((col_threads<T>(N)), (sizeof(T) == 4 ? 4 : 2))
   const FieldRec en = ents[blockIdx.y];
   const int tid = threadIdx.x, c = tid % TC, t = tid / TC;
   const bool live = N % TC == 0 || c0 + c < N;
-  const size_t base = (size_t)kz * field_plane_stride<T>(N) + (live ? c0 + c : N - 1);
-  cx<T>* b0 = reinterpret_cast<cx<T>*>(en.p0);
-  cx<T>* b1 = reinterpret_cast<cx<T>*>(en.p1);
-  const bool pair = b1 != nullptr;
+  // (uniform row bases and one 32-bit offset a thread: 64-bit addresses per row would spill)
+  const unsigned off = (unsigned)(t * N + (live ? c0 + c : N - 1));
+  const bool pair = en.p1 != nullptr;
+  const size_t plane = (size_t)kz * field_plane_stride<T>(N);
+  cx<T>* b0 = reinterpret_cast<cx<T>*>(en.p0) + plane;
+  cx<T>* b1 = reinterpret_cast<cx<T>*>(en.p1) + plane;
   cx<T> u[E], v[E];
 #pragma unroll
-  for (int e = 0; e < E; ++e) u[e] = gload<T>(b0, base + (t + PT * e) * N);
+  for (int e = 0; e < E; ++e) u[e] = gload32<T>(b0 + PT * e * N, off);
   if (pair) {
 #pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = gload<T>(b1, base + (t + PT * e) * N);
+    for (int e = 0; e < E; ++e) v[e] = gload32<T>(b1 + PT * e * N, off);
   }
   ct_twiddles<T, E, N, N>(twst, tw);
   auto put = [&](cx<T>* b, const cx<T>* w) {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int r = t + PT * e, f = r - (e >= E / 2 ? N : 0);
-      if (live && f * f + kz * kz < tmax) gstore<T>(b, base + r * N, w[e]);
+      if (live && f * f + kz * kz < tmax) gstore32<T>(b + PT * e * N, off, w[e]);
     }
   };
   if (pair) {
