@@ -76,12 +76,13 @@ struct BinSpec {
   int thr_lds;           // stage the thresholds in LDS
 };
 
-// Catalog sums: out2[0] = sum w^2, out2[1] = sum w^2 nbar, *wmax = max |w| (w, nbar may be
-// null => 1).  partial holds 3 nblk doubles.
-hipError_t launch_catalog_sums(const double* w, const double* nbar, int64_t n, double* partial, int nblk,
-                               double* out2, double* wmax, hipStream_t s);
+// Sums of ncat (1 or 2) catalogs: out2[2 c] = sum w^2, out2[2 c + 1] = sum w^2 nbar, wmax[c] = max |w| (w, nbar
+// may be null => 1).  partial holds 3 nblk doubles a catalog.
+hipError_t launch_catalog_sums(const double* const* w, const double* const* nbar, const int64_t* n, int ncat,
+                               double* partial, int nblk, double* out2, double* wmax, hipStream_t s);
 
-template <typename T> hipError_t launch_fill(T* p, size_t n, T v, hipStream_t s);
+// n values each of p and, where it is not null, p1.
+template <typename T> hipError_t launch_fill(T* p, T* p1, size_t n, T v, hipStream_t s);
 
 // How the particles are sorted by the tile of their base node.  The counters are `rows` rows of `pitch`: with
 // chunk > 0 one row per chunk of that many particles, counted in LDS; else TILE_COUNT_COPIES rows of global

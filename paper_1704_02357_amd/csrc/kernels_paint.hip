@@ -13,9 +13,17 @@ namespace {
 
 constexpr int SUM_THREADS = 256;
 
-__global__ void __launch_bounds__(SUM_THREADS) k_catalog_sums(const double* __restrict__ w,
-                                                              const double* __restrict__ nbar, int64_t n,
-                                                              double* __restrict__ partial) {
+// The sums of both catalogs in one launch each (blockIdx.y, and blockIdx.x of the second kernel, is the
+// catalog): on small meshes launches are a good part of an estimate.
+struct SumArgs {
+  const double *w[2], *nbar[2];
+  int64_t n[2];
+};
+__global__ void __launch_bounds__(SUM_THREADS) k_catalog_sums(SumArgs args, double* __restrict__ partial) {
+  const double* __restrict__ w = args.w[blockIdx.y];
+  const double* __restrict__ nbar = args.nbar[blockIdx.y];
+  const int64_t n = args.n[blockIdx.y];
+  partial += 3 * (size_t)gridDim.x * blockIdx.y;
   __shared__ double s0[SUM_THREADS], s1[SUM_THREADS], s2[SUM_THREADS];
   double a0 = 0.0, a1 = 0.0, a2 = 0.0;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -47,6 +55,9 @@ __global__ void __launch_bounds__(SUM_THREADS) k_catalog_sums(const double* __re
 
 __global__ void __launch_bounds__(SUM_THREADS) k_sum_partials2(const double* __restrict__ partial, int nblk,
                                                                double* __restrict__ out2, double* __restrict__ wmax) {
+  partial += 3 * (size_t)nblk * blockIdx.x;
+  out2 += 2 * blockIdx.x;
+  wmax += blockIdx.x;
   __shared__ double s0[SUM_THREADS], s1[SUM_THREADS], s2[SUM_THREADS];
   double a0 = 0.0, a1 = 0.0, a2 = 0.0;
   for (int b = threadIdx.x; b < nblk; b += SUM_THREADS) {
@@ -74,7 +85,8 @@ __global__ void __launch_bounds__(SUM_THREADS) k_sum_partials2(const double* __r
 }
 
 template <typename T>
-__global__ void k_fill(T* __restrict__ p, size_t n, T v) {
+__global__ void k_fill(T* __restrict__ p0, T* __restrict__ p1, size_t n, T v) {
+  T* p = blockIdx.y ? p1 : p0;
   const size_t stride = (size_t)gridDim.x * blockDim.x;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
 }
@@ -291,6 +303,39 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_add(const int* __restrict
       start += v[c];
     }
   }
+}
+
+// The three steps in one launch, by one block: where all the counters are few.
+constexpr int SCAN_ONE = 1 << 16;
+__global__ void __launch_bounds__(SUMS_THREADS) k_scan_one(int n, int rows, int pitch, int* __restrict__ off,
+                                                           int* __restrict__ count) {
+  __shared__ int part[SUMS_THREADS];
+  __shared__ int carry;
+  if (threadIdx.x == 0) carry = 0;
+  __syncthreads();
+  for (int base = 0; base < n; base += SUMS_THREADS) {
+    const int i = base + threadIdx.x;
+    int v = 0;
+    if (i < n)
+      for (int c0 = 0; c0 < rows; c0 += SCAN_ROWS) {
+#pragma unroll
+        for (int c = 0; c < SCAN_ROWS; ++c) v += c0 + c < rows ? count[(size_t)(c0 + c) * pitch + i] : 0;
+      }
+    const int ex = block_scan_excl<SUMS_THREADS>(v, part);
+    int start = carry + ex;
+    if (i < n) {
+      off[i] = start;
+      for (int c = 0; c < rows; ++c) {
+        const int m = count[(size_t)c * pitch + i];
+        count[(size_t)c * pitch + i] = start;
+        start += m;
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x == SUMS_THREADS - 1) carry += ex + v;
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) off[n] = carry;
 }
 
 // Scatter each particle's payload (x, y, z, signed weight) to its slot in tile order.  The row of a
@@ -608,20 +653,26 @@ __global__ void k_det_convert(const unsigned long long* __restrict__ acc, T* __r
 
 }  // namespace
 
-hipError_t launch_catalog_sums(const double* w, const double* nbar, int64_t n, double* partial, int nblk,
-                               double* out2, double* wmax, hipStream_t s) {
-  k_catalog_sums<<<nblk, SUM_THREADS, 0, s>>>(w, nbar, n, partial);
+hipError_t launch_catalog_sums(const double* const* w, const double* const* nbar, const int64_t* n, int ncat,
+                               double* partial, int nblk, double* out2, double* wmax, hipStream_t s) {
+  SumArgs args{};
+  for (int c = 0; c < ncat; ++c) {
+    args.w[c] = w[c];
+    args.nbar[c] = nbar[c];
+    args.n[c] = n[c];
+  }
+  k_catalog_sums<<<dim3(nblk, ncat), SUM_THREADS, 0, s>>>(args, partial);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_sum_partials2<<<1, SUM_THREADS, 0, s>>>(partial, nblk, out2, wmax);
+  k_sum_partials2<<<ncat, SUM_THREADS, 0, s>>>(partial, nblk, out2, wmax);
   return hipGetLastError();
 }
 
-template <typename T> hipError_t launch_fill(T* p, size_t n, T v, hipStream_t s) {
+template <typename T> hipError_t launch_fill(T* p, T* p1, size_t n, T v, hipStream_t s) {
   if (n == 0) return hipSuccess;
   size_t blocks = (n + 255) / 256;
   if (blocks > 8192) blocks = 8192;
-  k_fill<T><<<(unsigned)blocks, 256, 0, s>>>(p, n, v);
+  k_fill<T><<<dim3((unsigned)blocks, p1 ? 2 : 1), 256, 0, s>>>(p, p1, n, v);
   return hipGetLastError();
 }
 
@@ -681,9 +732,13 @@ hipError_t launch_tile_sort(const TileSort& t, const double* origin, double scal
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int nblk = (t.keys + SCAN_THREADS - 1) / SCAN_THREADS;
-  k_scan_blocks<<<nblk, SCAN_THREADS, 0, s>>>(count, t.keys, t.rows, t.pitch, off, bsum);
-  k_scan_sums<<<1, SUMS_THREADS, 0, s>>>(bsum, nblk, off, t.keys);
-  k_scan_add<<<nblk, SCAN_THREADS, 0, s>>>(bsum, t.keys, t.rows, t.pitch, off, count);
+  if ((int64_t)t.rows * t.pitch <= SCAN_ONE) {
+    k_scan_one<<<1, SUMS_THREADS, 0, s>>>(t.keys, t.rows, t.pitch, off, count);
+  } else {
+    k_scan_blocks<<<nblk, SCAN_THREADS, 0, s>>>(count, t.keys, t.rows, t.pitch, off, bsum);
+    k_scan_sums<<<1, SUMS_THREADS, 0, s>>>(bsum, nblk, off, t.keys);
+    k_scan_add<<<nblk, SCAN_THREADS, 0, s>>>(bsum, t.keys, t.rows, t.pitch, off, count);
+  }
   e = hipGetLastError();
   if (e != hipSuccess || ntot == 0) return e;
   const int64_t blocks = std::min<int64_t>((ntot + 256 * CPT - 1) / (256 * CPT), 16384);
@@ -748,9 +803,9 @@ template hipError_t launch_det_convert<float>(const unsigned long long*, float*,
                                               hipStream_t);
 template hipError_t launch_det_convert<double>(const unsigned long long*, double*, double*, int, const double*,
                                                hipStream_t);
-template hipError_t launch_fill<unsigned long long>(unsigned long long*, size_t, unsigned long long, hipStream_t);
-template hipError_t launch_fill<float>(float*, size_t, float, hipStream_t);
-template hipError_t launch_fill<int>(int*, size_t, int, hipStream_t);
-template hipError_t launch_fill<double>(double*, size_t, double, hipStream_t);
+template hipError_t launch_fill<unsigned long long>(unsigned long long*, unsigned long long*, size_t, unsigned long long, hipStream_t);
+template hipError_t launch_fill<float>(float*, float*, size_t, float, hipStream_t);
+template hipError_t launch_fill<int>(int*, int*, size_t, int, hipStream_t);
+template hipError_t launch_fill<double>(double*, double*, size_t, double, hipStream_t);
 
 }  // namespace pkm

@@ -94,7 +94,7 @@ struct pkm_plan {
   size_t partial_cap = 0;  // doubles
   double* out_dev = nullptr;
   size_t out_cap = 0;
-  double* sums_dev = nullptr;  // 4 sums, the 2 catalogs' max |w|, 3 x SUM_BLOCKS partials
+  double* sums_dev = nullptr;  // 4 sums, the 2 catalogs' max |w|, 2 x 3 x SUM_BLOCKS partials
   unsigned long long* det_acc = nullptr;  // deterministic mode: 64-bit paint accumulators
   double* det_scale = nullptr;            // deterministic mode: the shared fixed-point scale
   double* cat_dev = nullptr;   // staging for host catalogs
@@ -507,13 +507,11 @@ template <typename T> void enqueue_paint(pkm_plan* pl, const DevCats& dc) {
   {
     StageScope ss(pl, PKM_STAGE_SUMS);
     // sums_dev: [0..3] the sums of both catalogs, [4], [5] their largest |w|, then partials
-    check_hip(pl, launch_catalog_sums(dc.dw, nullptr, dc.nd, pl->sums_dev + 6, SUM_BLOCKS, pl->sums_dev,
+    const double *w[2] = {dc.dw, dc.rw}, *nbar[2] = {nullptr, dc.rn};
+    const int64_t cnt[2] = {dc.nd, dc.nr};
+    check_hip(pl, launch_catalog_sums(w, nbar, cnt, has_r ? 2 : 1, pl->sums_dev + 6, SUM_BLOCKS, pl->sums_dev,
                                       pl->sums_dev + 4, s),
               "sums");
-    if (has_r)
-      check_hip(pl, launch_catalog_sums(dc.rw, dc.rn, dc.nr, pl->sums_dev + 6, SUM_BLOCKS, pl->sums_dev + 2,
-                                        pl->sums_dev + 5, s),
-                "sums");
   }
   T* d1 = (T*)pl->d1;
   T* d2 = pl->p.interlaced ? (T*)pl->d2 : nullptr;
@@ -530,12 +528,11 @@ template <typename T> void enqueue_paint(pkm_plan* pl, const DevCats& dc) {
   {
     StageScope ss(pl, PKM_STAGE_FILL);
     if (ts.chunk == 0)
-      check_hip(pl, launch_fill<int>(pl->tile_count, (size_t)TILE_COUNT_COPIES * (pl->ntiles + 1), 0, s), "fill");
+      check_hip(pl, launch_fill<int>(pl->tile_count, nullptr, (size_t)TILE_COUNT_COPIES * (pl->ntiles + 1), 0, s), "fill");
     if (det) {
-      check_hip(pl, launch_fill<unsigned long long>(pl->det_acc, cells * (d2 ? 2 : 1), 0ull, s), "fill");
+      check_hip(pl, launch_fill<unsigned long long>(pl->det_acc, nullptr, cells * (d2 ? 2 : 1), 0ull, s), "fill");
     } else {
-      check_hip(pl, launch_fill<T>(d1, cells, T(0), s), "fill");
-      if (d2) check_hip(pl, launch_fill<T>(d2, cells, T(0), s), "fill");
+      check_hip(pl, launch_fill<T>(d1, d2, cells, T(0), s), "fill");
     }
   }
   {
@@ -806,7 +803,7 @@ template <typename T> void enqueue_compute(pkm_plan* pl) {
   hipStream_t s = pl->stream;
   const ComputeCfg& cc = pl->cc;
   const int n = pl->p.nmesh;
-  check_hip(pl, launch_fill<double>(pl->out_dev, cc.total_vals, 0.0, s), "zero out");
+  check_hip(pl, launch_fill<double>(pl->out_dev, nullptr, cc.total_vals, 0.0, s), "zero out");
   const bool dc_real = !(pl->p.interlaced || pl->p.compensated);
   const double off[3] = {pl->p.box_origin[0] - pl->p.observer[0], pl->p.box_origin[1] - pl->p.observer[1],
                          pl->p.box_origin[2] - pl->p.observer[2]};
@@ -1522,7 +1519,7 @@ pkm_status pkm_plan_create_shaped(const pkm_params* p, const pkm_device* dev, co
     pl->invw = dalloc(pl, pl->es * n);
     pl->phase = dalloc(pl, 2 * pl->es * n);
     pl->ytab = dalloc(pl, pl->es * (YLM_LMAX + 1) * YLM_STRIDE);
-    pl->sums_dev = (double*)dalloc(pl, sizeof(double) * (6 + 3 * SUM_BLOCKS));
+    pl->sums_dev = (double*)dalloc(pl, sizeof(double) * (6 + 2 * 3 * SUM_BLOCKS));
     if (pl->p.deterministic) {
       pl->det_acc = (unsigned long long*)dalloc(pl, sizeof(unsigned long long) * (size_t)n * n * n *
                                                         (p->interlaced ? 2 : 1));
