@@ -10,7 +10,8 @@ namespace {
 
 // Elements per thread, columns and threads of the compile-time column passes: N / E rows by 16 columns
 // (128-byte rows in FP32, 256 in FP64), 8 where that exceeds 1024 threads or the LDS of a CU.  Rows of 64 bytes
-// fetch their 128-byte lines twice: 1024^3 combine 7.35 -> 6.32 ms.
+// fetch their 128-byte lines twice: 1024^3 combine 7.35 -> 6.32 ms
+// (5.87 since its rows have uniform bases).
 __host__ __device__ constexpr int col_e(int n) { return is_pow2(n) ? (n >= 256 ? 16 : 8) : 12; }
 template <typename T> __host__ __device__ constexpr int col_tile(int n) {
   return (n / col_e(n)) * 16 > (sizeof(T) == 4 ? 1024 : 512) || sizeof(cx<T>) * ((size_t)n * 17 + n) > 160 * 1024 ? 8 : 16;
@@ -41,13 +42,14 @@ __global__ void __launch_bounds__((NC > 0 ? (NC / E) * TC : XMAX_THREADS)) k_col
   const int pitch = tile + 1;
   const int tid = threadIdx.x;
   const int c = tid % tile, t = tid / tile;
-  const size_t base = (size_t)outer * outer_stride + c0 + c;
+  buf += (size_t)outer * outer_stride + c0;
+  const unsigned off = (unsigned)(t * row_stride + c);
   constexpr bool FULL = NC > 0 && (NC / 2) % (TC > 0 ? TC : 1) == 0;
   const bool live = FULL || c0 + c < clen;
   cx<T> u[E];
 #pragma unroll
   for (int e = 0; e < E; ++e)
-    u[e] = live ? gload<T>(buf, base + (size_t)(t + pt * e) * row_stride) : mk<T>(T(0), T(0));
+    u[e] = live ? gload32<T>(buf + pt * e * row_stride, off) : mk<T>(T(0), T(0));
   // generic path: the W_N^j table; compile-time path: the per-stage table only
   cx<T>* twl = lds + (size_t)n * pitch;
   cx<T>* twst = twl;
@@ -56,7 +58,7 @@ __global__ void __launch_bounds__((NC > 0 ? (NC / E) * TC : XMAX_THREADS)) k_col
   xf_regs<T, E, INV, 0, NC, false>(lds, c, pitch, rt, t, u, twst, twl);
   if (!live) return;
 #pragma unroll
-  for (int e = 0; e < E; ++e) gstore<T>(buf, base + (size_t)(t + pt * e) * row_stride, u[e]);
+  for (int e = 0; e < E; ++e) gstore32<T>(buf + pt * e * row_stride, off, u[e]);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -122,7 +124,8 @@ __global__ void __launch_bounds__((col_threads<T>(N)), (sizeof(T) == 4 ? 4 : 2))
 }
 
 // ------------------------------------------------------------------------------------------
-// x pass of the painted meshes + combine + inverse x of C (same lane layout as k_col)
+// x pass of the painted meshes + combine + inverse x of C (same lane layout as k_col).  512^3 FP32: 0.60 ms for
+// 2.1 GB; three transforms in a row on 16 wavefronts a CU leave the memory idle for part of the time.
 // ------------------------------------------------------------------------------------------
 template <typename T, int E, int NC, int TC>
 __global__ void __launch_bounds__((NC > 0 ? (NC / E) * TC : XMAX_THREADS), (sizeof(T) == 4 ? 4 : 2)) k_xcombine(int n_rt, int tile_rt, uint32_t sched, int nst,
@@ -149,14 +152,15 @@ __global__ void __launch_bounds__((NC > 0 ? (NC / E) * TC : XMAX_THREADS), (size
   constexpr bool FULL = NC > 0 && (NC / 2) % (TC > 0 ? TC : 1) == 0;
   const bool live = FULL || kz0 + c < nh;
   const int kz = live ? kz0 + c : nh - 1;  // lanes past the row repeat its last column and write nothing
-  const size_t base = (size_t)y * nh + kz;
+  const size_t base = (size_t)y * nh;
+  const unsigned off = (unsigned)(t * rs + kz);
   cx<T> a1[E];
   cx<T> a2[E];
 #pragma unroll
-  for (int e = 0; e < E; ++e) a1[e] = gload<T>(s1, base + (size_t)(t + pt * e) * rs);
+  for (int e = 0; e < E; ++e) a1[e] = gload32<T>(s1 + base + pt * e * rs, off);
   if (interlaced) {
 #pragma unroll
-    for (int e = 0; e < E; ++e) a2[e] = gload<T>(s2, base + (size_t)(t + pt * e) * rs);
+    for (int e = 0; e < E; ++e) a2[e] = gload32<T>(s2 + base + pt * e * rs, off);
   }
   // generic path: the W_N^j table; compile-time path: the per-stage table only
   cx<T>* twl = lds + (size_t)n * pitch;
@@ -182,13 +186,13 @@ __global__ void __launch_bounds__((NC > 0 ? (NC / E) * TC : XMAX_THREADS), (size
     if (compensated) v = cscale<T>(v, invw[x] * invw[y] * invw[kz]);
     if (ynyq || x == nh) v = mk<T>(T(0), T(0));
     a1[e] = v;
-    if (live) gstore<T>(cout, base + (size_t)x * rs, v);
+    if (live) gstore32<T>(cout + base + pt * e * rs, off, v);
   }
   if (gout == nullptr) return;
   xf_regs<T, E, true, 0, NC, false>(lds, c, pitch, rt, t, a1, twst, twl);
   if (!live) return;
 #pragma unroll
-  for (int e = 0; e < E; ++e) gstore<T>(gout, base + (size_t)(t + pt * e) * rs, a1[e]);
+  for (int e = 0; e < E; ++e) gstore32<T>(gout + base + pt * e * rs, off, a1[e]);
 }
 
 }  // namespace
