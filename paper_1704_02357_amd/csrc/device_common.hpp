@@ -576,7 +576,7 @@ template <typename T, int NV> __device__ __forceinline__ void hrun_init(HRun<T, 
 }
 
 // dir(v, &x, &y, &z): the unit vector of point v.
-template <typename T, int NV, bool TIGHT = false, typename DIR>
+template <typename T, int NV, typename DIR>
 __device__ __forceinline__ void hrun_to(HRun<T, NV>& s, int ell, int am, T f, const T* __restrict__ tab, DIR dir) {
   if (am != s.am || s.l < am || ell < s.l) {
     for (int j = s.am; j < am; ++j) {
@@ -587,7 +587,6 @@ __device__ __forceinline__ void hrun_to(HRun<T, NV>& s, int ell, int am, T f, co
         const T nr = s.cr[v] * x - s.ci[v] * y;
         s.ci[v] = s.cr[v] * y + s.ci[v] * x;
         s.cr[v] = nr;
-        if (TIGHT) __builtin_amdgcn_sched_barrier(0);
       }
     }
     s.am = am;
@@ -609,7 +608,6 @@ __device__ __forceinline__ void hrun_to(HRun<T, NV>& s, int ell, int am, T f, co
       dir(v, x, y, z);
       s.q0[v] = a1 * z * s.q1[v] - b1 * s.q0[v];  // q_l
       s.q1[v] = a2 * z * s.q0[v] - b2 * s.q1[v];  // q_{l+1}
-      if (TIGHT) __builtin_amdgcn_sched_barrier(0);
     }
   }
   if (l <= ell) {
@@ -622,10 +620,62 @@ __device__ __forceinline__ void hrun_to(HRun<T, NV>& s, int ell, int am, T f, co
       const T q2 = a * z * s.q1[v] - b * s.q0[v];
       s.q0[v] = s.q1[v];
       s.q1[v] = q2;
-      if (TIGHT) __builtin_amdgcn_sched_barrier(0);
     }
   }
   s.l = ell;
+}
+
+// The same at one degree, for |m| in ascending order: q at (ell, am) from q_am^am upwards each time, so that
+// between calls only the powers and q live in registers.  The caller starts with cr = 1, ci = 0, am = -1.
+// TIGHT keeps the points apart (fewest registers at once).
+template <typename T, int NV> struct HFixed {
+  T cr[NV], ci[NV], q[NV];
+  int am;
+};
+template <typename T, int NV, bool TIGHT, typename DIR>
+__device__ __forceinline__ void hfixed_to(HFixed<T, NV>& s, int ell, int am, const T* __restrict__ tab, DIR dir) {
+  if (am == s.am) return;
+  for (int j = s.am < 0 ? 0 : s.am; j < am; ++j) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      T x, y, z;
+      dir(v, x, y, z);
+      const T nr = s.cr[v] * x - s.ci[v] * y;
+      s.ci[v] = s.cr[v] * y + s.ci[v] * x;
+      s.cr[v] = nr;
+      if (TIGHT) __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  s.am = am;
+  const T* c = tab + am * YLM_STRIDE;
+  T p[NV];
+  const T c0 = c[0];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) { s.q[v] = c0; p[v] = T(0); }
+  int j = 1;
+  // two degrees per iteration with the pair's roles swapped in between (no register copies)
+  for (; j + 1 <= ell - am; j += 2) {
+    const T a1 = c[2 * j - 1], b1 = c[2 * j];  // b = 0 for j = 1
+    const T a2 = c[2 * j + 1], b2 = c[2 * j + 2];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      T x, y, z;
+      dir(v, x, y, z);
+      p[v] = a1 * z * s.q[v] - b1 * p[v];
+      s.q[v] = a2 * z * p[v] - b2 * s.q[v];
+      if (TIGHT) __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  if (j <= ell - am) {
+    const T a = c[2 * j - 1], b = c[2 * j];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      T x, y, z;
+      dir(v, x, y, z);
+      s.q[v] = a * z * s.q[v] - b * p[v];
+      if (TIGHT) __builtin_amdgcn_sched_barrier(0);
+    }
+  }
 }
 
 // Atomic add to an LDS location (native ds_add_f32 / ds_add_f64; a plain atomicAdd through a

@@ -30,6 +30,10 @@ template <typename T, int N> struct PostShape {
   static constexpr bool TIGHT = N > 128;
   // wavefronts per SIMD the registers are bounded for
   static constexpr int MINW = sizeof(T) == 4 ? (E <= 8 && N > 128 ? 3 : 2) : (E <= 8 && N > 128 ? 2 : 1);
+  // Merge the l = 0 values of neighbouring lanes before their atomics: 512^3 1.61 -> 1.33 ms (merging the values of
+  // the other slots as well: 1.36).  12 and 16 points a thread spill more for it (432^3 1.57 -> 1.64, 1024^3 21.0 ->
+  // 22.8 ms).
+  static constexpr bool MERGE = E <= 8;
   // persistent blocks per CU (threads the registers above leave room for)
   static constexpr int PER_CU = (256 * MINW) / (((THREADS + 63) / 64) * 64) > 0
                                     ? (256 * MINW) / (((THREADS + 63) / 64) * 64) : 1;
@@ -81,6 +85,21 @@ template <int E> __device__ __forceinline__ void kbins(const int* thr, int nb, c
   for (int e = 0; e < E; ++e) bin[e] = n2[e] >= lo && n2[e] < top ? bin[e] : -1;
 }
 
+// Neighbouring lanes hold neighbouring y, whose modes are often in one bin, and their atomics on it are done
+// one after the other.  Lanes that are partners in a quad (CTRL: the quad permutation, 0xB1 and 0x4E pair lanes 1
+// and 2 apart) and share a bin add their values first: the lower lane takes the sum, the upper one no bin.
+template <int CTRL> __device__ __forceinline__ int quad_from(int v) {
+  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL> __device__ __forceinline__ double quad_from(double v) {
+  return __hiloint2double(quad_from<CTRL>(__double2hiint(v)), quad_from<CTRL>(__double2loint(v)));
+}
+template <int CTRL, typename... V> __device__ __forceinline__ void quad_merge(int& bin, V&... v) {
+  const bool same = quad_from<CTRL>(bin) == bin;
+  ((v += same ? quad_from<CTRL>(v) : V(0)), ...);
+  if (same && (threadIdx.x & (CTRL == 0xB1 ? 1 : 2))) bin = 0xffff;
+}
+
 // ------------------------------------------------------------------------------------------
 // The post-pass.  Thread (t, c) transforms line kz0 + c and holds y = t + PT e, the transform's own
 // register layout, so each line is loaded straight into registers (whole contiguous lines, the
@@ -90,10 +109,10 @@ template <int E> __device__ __forceinline__ void kbins(const int* thr, int nb, c
 // bins after the slot's last line.  Only tiles that hold modes below the last k edge are listed
 // (`tiles`, x and kz0 packed).  Registers bound the wavefronts in flight: the unit vectors are rebuilt
 // from the mode numbers (linear in fy) where the recurrence needs them.
-// 512^3, 14 fields of l <= 4: 2.64 ms as packed half lines over every mode, 1.86 now (3.2 TB/s; the rest is
-// the harmonics and the exchanges); 432^3, 15 of the 45 fields of l <= 8: 5.85 -> 1.63 ms (a kernel of run-time
-// lengths before); 384^3 FP64 2.60 -> 1.62 ms; 256^3 337 -> 251 us.  128^3, 289 fields of l <= 16:
-// 322 -> 418 us, 64^3 FP64 30 -> 39 us: there a full line has half the wavefronts of a packed one.
+// 512^3, 14 fields of l <= 4: 2.64 ms as packed half lines over every mode, 1.33 now (4.5 TB/s; the rest is
+// the harmonics and the exchanges); 432^3, 15 of the 45 fields of l <= 8: 5.85 -> 1.57 ms (a kernel of run-time
+// lengths before); 1024^3 19.0 -> 14.9; 384^3 FP64 2.60 -> 1.6; 256^3 337 -> 221 us.  128^3, 289 fields of
+// l <= 16: 322 -> 390 us, 64^3 FP64 30 -> 37 us: there a full line has half the wavefronts of a packed one.
 // ------------------------------------------------------------------------------------------
 template <typename T, int N, bool CART>
 __global__ void __launch_bounds__((PostShape<T, N>::THREADS), (PostShape<T, N>::MINW))
@@ -188,14 +207,14 @@ __global__ void __launch_bounds__((PostShape<T, N>::THREADS), (PostShape<T, N>::
     const unsigned tl_next = tiles[walk.tile(j + walk.step < walk.end ? j + walk.step : j)];
     for (int li = 0, slot = 0; slot < nslots || (slot == 0 && with_l0); ++slot) {
       cx<T> acc[E];
-      HRun<T, E> hr;
+      HFixed<T, E> hr;
+      hr.am = -1;
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         acc[e] = mk<T>(T(0), T(0));
         hr.cr[e] = T(1);
         hr.ci[e] = T(0);
       }
-      hrun_init(hr);
       const int l_slot = rec.l;
       for (; li < nrecs && rec.slot == slot; ++li) {
         const int l = rec.l, m = rec.m;
@@ -208,13 +227,13 @@ __global__ void __launch_bounds__((PostShape<T, N>::THREADS), (PostShape<T, N>::
         __builtin_amdgcn_sched_barrier(0);  // (the last stage's inputs and twiddles are not held across the harmonics)
         T y[E];
         if constexpr (!CART) {
-          hrun_to<T, E, S::TIGHT>(hr, l, m < 0 ? -m : m, T(1), ytab, dir);
+          hfixed_to<T, E, S::TIGHT>(hr, l, m < 0 ? -m : m, ytab, dir);
           if (m < 0) {
 #pragma unroll
-            for (int e = 0; e < E; ++e) y[e] = hr.q1[e] * hr.ci[e];
+            for (int e = 0; e < E; ++e) y[e] = hr.q[e] * hr.ci[e];
           } else {
 #pragma unroll
-            for (int e = 0; e < E; ++e) y[e] = hr.q1[e] * hr.cr[e];
+            for (int e = 0; e < E; ++e) y[e] = hr.q[e] * hr.cr[e];
           }
         } else {
           monomial_eval<T, E>(l, m, (T)multinomial(l, m), dir, y);
@@ -234,19 +253,36 @@ __global__ void __launch_bounds__((PostShape<T, N>::THREADS), (PostShape<T, N>::
 #pragma unroll
           for (int e = 0; e < E; ++e) {
             if constexpr (S::TIGHT) __builtin_amdgcn_sched_barrier(0);
-            const int b = bin_of(e);
-            if (b == 0xffff) continue;
+            int b = bin_of(e);
+            if constexpr (!S::MERGE)
+              if (b == 0xffff) continue;
             const cx<T> cv = cst[c * S::CPITCH + t + PT * e];
             const double cr = cv.x, ci = cv.y;
-            if (nslots > 0) {
+            auto folded = [&]() {
               const double ar = acc[e].x, ai = acc[e].y;
-              lds_atomic_add<double>(&hs[b], wfold * (odd ? ci * ar - cr * ai : cr * ar + ci * ai));
-            }
-            if (l0) {
+              return wfold * (odd ? ci * ar - cr * ai : cr * ar + ci * ai);
+            };
+            auto k_sum = [&]() {
               const int fy = t + PT * e - (e >= E / 2 ? N : 0);
-              const int n2 = fx * fx + fy * fy + kz * kz;
+              return w * kf * sqrt((double)(fx * fx + fy * fy + kz * kz));
+            };
+            if (S::MERGE && l0) {  // (lanes with no bin stay: their neighbours read them)
+              int cnt = kz == 0 ? 1 : 2;
+              double v = folded(), ks = k_sum(), p0 = w * (cr * cr + ci * ci);
+              quad_merge<0xB1>(b, v, cnt, ks, p0);
+              quad_merge<0x4E>(b, v, cnt, ks, p0);
+              if (b == 0xffff) continue;
+              if (nslots > 0) lds_atomic_add<double>(&hs[b], v);
+              lds_atomic_add<double>(&h[b], (double)cnt);
+              lds_atomic_add<double>(&h[nb + b], ks);
+              lds_atomic_add<double>(&h[2 * nb + b], p0);
+              continue;
+            }
+            if (b == 0xffff) continue;
+            if (nslots > 0) lds_atomic_add<double>(&hs[b], folded());
+            if (l0) {
               lds_atomic_add<double>(&h[b], w);
-              lds_atomic_add<double>(&h[nb + b], w * kf * sqrt((double)n2));
+              lds_atomic_add<double>(&h[nb + b], k_sum());
               lds_atomic_add<double>(&h[2 * nb + b], w * (cr * cr + ci * ci));
             }
           }
