@@ -17,7 +17,8 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libpkm.so")
 
-KERNEL_SOURCES = ["kernels_post_f32.hip", "kernels_post_f64.hip", "kernels_pre_f32.hip", "kernels_pre_f64.hip",
+KERNEL_SOURCES = ["kernels_post_f32.hip", "kernels_post_f64.hip", "kernels_post_few_f32.hip",
+                  "kernels_post_few_f64.hip", "kernels_pre_f32.hip", "kernels_pre_f64.hip",
                   "kernels_col_f32.hip", "kernels_col_f64.hip", "kernels_fft.hip", "kernels_paint.hip"]
 SOURCES = KERNEL_SOURCES + ["plan.hip", "runtime.hip", "host_math.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -24,7 +24,10 @@ template <typename T, int N> struct PostShape {
   static constexpr int THREADS = PT * TP;
   static constexpr int PITCH = ct_line_slots<T, E, N>();
   static constexpr int CPITCH = N + 1;  // the tile's C, [line][y]
-  static constexpr size_t SMEM = sizeof(cx<T>) * ((size_t)TP * (PITCH + CPITCH) + twst_size<E, N>());
+  // LDS of a block of `tp` lines without histograms and thresholds
+  __host__ __device__ static constexpr size_t smem(int tp) {
+    return sizeof(cx<T>) * ((size_t)tp * (PITCH + CPITCH) + twst_size<E, N>());
+  }
   // Sides to 128 leave a few wavefronts per SIMD for the whole grid: latency bounds them, so they keep
   // the points' chains interleaved; longer ones keep the registers low.
   static constexpr bool TIGHT = N > 128;
@@ -34,9 +37,11 @@ template <typename T, int N> struct PostShape {
   // the other slots as well: 1.36).  12 and 16 points a thread spill more for it (432^3 1.57 -> 1.64, 1024^3 21.0 ->
   // 22.8 ms).
   static constexpr bool MERGE = E <= 8;
-  // persistent blocks per CU (threads the registers above leave room for)
-  static constexpr int PER_CU = (256 * MINW) / (((THREADS + 63) / 64) * 64) > 0
-                                    ? (256 * MINW) / (((THREADS + 63) / 64) * 64) : 1;
+  // persistent blocks of `tp` lines per CU (threads the registers above leave room for)
+  static constexpr int per_cu(int tp) {
+    const int wide = (PT * tp + 63) / 64 * 64;
+    return 256 * MINW / wide > 0 ? 256 * MINW / wide : 1;
+  }
 };
 
 // Tiles of a persistent post-pass block.  When the tile count and the grid are multiples of
@@ -113,20 +118,23 @@ template <int CTRL, typename... V> __device__ __forceinline__ void quad_merge(in
 // the harmonics and the exchanges); 432^3, 15 of the 45 fields of l <= 8: 5.85 -> 1.57 ms (a kernel of run-time
 // lengths before); 1024^3 19.0 -> 14.9; 384^3 FP64 2.60 -> 1.6; 256^3 337 -> 221 us.  128^3, 289 fields of
 // l <= 16: 322 -> 390 us, 64^3 FP64 30 -> 37 us: there a full line has half the wavefronts of a packed one.
+// ALL: blocks of all TP lines.  Else of as many (fewer) as the launch has threads for: requests whose
+// histograms leave no room for TP lines in the LDS of a CU.
 // ------------------------------------------------------------------------------------------
-template <typename T, int N, bool CART>
+template <typename T, int N, bool CART, bool ALL>
 __global__ void __launch_bounds__((PostShape<T, N>::THREADS), (PostShape<T, N>::MINW))
     k_xpost(int nrecs, const FieldRec* __restrict__ recs, int nslots, int with_l0,
             double kf, const cx<T>* __restrict__ cin, const T* __restrict__ ytab, const int* __restrict__ thr,
             int nb, int copies, int turns, int thr_lds, double* __restrict__ partial,
             const cx<T>* __restrict__ tw, Frame frm, const unsigned* __restrict__ tiles, int ntiles) {
   using S = PostShape<T, N>;
-  constexpr int E = S::E, PT = S::PT, TP = S::TP, nh = N / 2;
+  constexpr int E = S::E, PT = S::PT, nh = N / 2;
+  const int TP = ALL ? S::TP : (int)blockDim.x / PT;
   extern __shared__ __align__(16) unsigned char smem[];
   cx<T>* exch = reinterpret_cast<cx<T>*>(smem);
   cx<T>* cst = exch + TP * S::PITCH;
   cx<T>* twst = cst + TP * S::CPITCH;
-  double* hist = reinterpret_cast<double*>(smem + S::SMEM);
+  double* hist = reinterpret_cast<double*>(smem + S::smem(TP));
   const int l0rows = with_l0 ? 3 : 0;
   const int nvals = (l0rows + nslots) * nb;
   int* thr_l = reinterpret_cast<int*>(hist + (size_t)copies * nvals);
@@ -150,7 +158,7 @@ __global__ void __launch_bounds__((PostShape<T, N>::THREADS), (PostShape<T, N>::
   auto fetch = [&](unsigned tl, const void* buf) {
     const int kz0 = (int)(tl & 0xffff);
     const cx<T>* b = reinterpret_cast<const cx<T>*>(buf) + (size_t)kz0 * plane + (size_t)(tl >> 16) * N;
-    const int cc = nh % TP == 0 || kz0 + c < nh ? c : nh - 1 - kz0;
+    const int cc = (ALL && nh % S::TP == 0) || kz0 + c < nh ? c : nh - 1 - kz0;
     const unsigned off = (unsigned)(cc * plane + t);
 #pragma unroll
     for (int e = 0; e < E; ++e) nxt[e] = gload32<T>(b, off + (unsigned)(PT * e));
@@ -167,7 +175,7 @@ __global__ void __launch_bounds__((PostShape<T, N>::THREADS), (PostShape<T, N>::
     __syncthreads();  // the previous tile's reads of it are done
 #pragma unroll
     for (int q = 0; q < E; ++q) {
-      const int i = tid + q * S::THREADS, y = i / TP, cc = i % TP;
+      const int i = tid + q * (PT * TP), y = i / TP, cc = i % TP;
       const int k = kz0 + cc < nh ? kz0 + cc : nh - 1;
       cst[cc * S::CPITCH + y] = gload32<T>(cin + (size_t)x * (N * nh), (unsigned)(y * nh + k));
     }
@@ -295,13 +303,34 @@ __global__ void __launch_bounds__((PostShape<T, N>::THREADS), (PostShape<T, N>::
   hist_flush(hist, copies, nvals, partial + (size_t)blockIdx.x * nvals);
 }
 
+// One launch of the post-pass of a side with blocks of `lines` lines: ALL blocks of all its lines, or fewer.
+template <typename T, int N, bool ALL>
+void post_run(int lines, int nrecs, const FieldRec* recs_dev, int nslots, int with_l0, const void* c_in,
+              const void* ytab, const BinSpec& bs, double kf, double* partial, int nblocks, const void* tw,
+              const Frame& frame, int basis, const unsigned* tiles_dev, int ntiles, hipStream_t s) {
+  using S = PostShape<T, N>;
+  const int nvals = ((with_l0 ? 3 : 0) + nslots) * bs.nb;
+  const size_t sm = S::smem(lines) + sizeof(double) * (size_t)bs.hist_copies * nvals +
+                    (bs.thr_lds ? sizeof(int) * (size_t)(bs.nb + 1) : 0);
+  auto run = [&](auto kern) {
+    kern<<<nblocks, S::PT * lines, sm, s>>>(nrecs, recs_dev, nslots, with_l0, kf, (const cx<T>*)c_in, (const T*)ytab,
+                                            bs.thr32, bs.nb, bs.hist_copies, bs.turns, bs.thr_lds, partial,
+                                            (const cx<T>*)tw, frame, tiles_dev, ntiles);
+  };
+  if (basis == 1) run(k_xpost<T, N, true, ALL>); else run(k_xpost<T, N, false, ALL>);
+}
+
 }  // namespace
 
-template <typename T> bool post_geometry(int n, PostGeometry* g) {
+#define PKM_POST_ARGS                                                                                        \
+  lines, nrecs, recs_dev, nslots, with_l0, c_in, ytab, bs, kf, partial, nblocks, tw, frame, basis, tiles_dev, ntiles, s
+
+template <typename T> bool post_geometry(int n, int lines, PostGeometry* g) {
 #define PKM_POST_SIDE(NV)                                                                                    \
   case NV: {                                                                                                 \
     using S = PostShape<T, NV>;                                                                              \
-    *g = PostGeometry{S::TP, S::THREADS, S::PER_CU, S::SMEM};                                                \
+    const int tp = lines > 0 && lines < S::TP ? lines : S::TP;                                               \
+    *g = PostGeometry{tp, S::PT * tp, S::per_cu(tp), S::smem(tp)};                                           \
     return true;                                                                                             \
   }
   switch (n) { PKM_FOR_SIDES(PKM_POST_SIDE) default: return false; }
@@ -309,23 +338,17 @@ template <typename T> bool post_geometry(int n, PostGeometry* g) {
 }
 
 template <typename T>
-hipError_t launch_xpost(const FftShape& fs, int nrecs, const FieldRec* recs_dev, int nslots, int with_l0,
+hipError_t launch_xpost(const FftShape& fs, int lines, int nrecs, const FieldRec* recs_dev, int nslots, int with_l0,
                         const void* c_in, const void* ytab, const BinSpec& bs, double kf,
                         double* partial, int nblocks, const void* tw, const Frame& frame, int basis,
                         const unsigned* tiles_dev, int ntiles, hipStream_t s) {
-  if (nslots < 0 || nblocks < 1) return hipErrorInvalidValue;
-  const int nvals = ((with_l0 ? 3 : 0) + nslots) * bs.nb;
+  if (nslots < 0 || nblocks < 1 || lines < 1) return hipErrorInvalidValue;
 #define PKM_POST_SIDE(NV)                                                                                    \
   case NV: {                                                                                                 \
-    using S = PostShape<T, NV>;                                                                              \
-    const size_t sm = S::SMEM + sizeof(double) * (size_t)bs.hist_copies * nvals +                            \
-                      (bs.thr_lds ? sizeof(int) * (size_t)(bs.nb + 1) : 0);                                  \
-    auto run = [&](auto kern) {                                                                              \
-      kern<<<nblocks, S::THREADS, sm, s>>>(                                                                  \
-          nrecs, recs_dev, nslots, with_l0, kf, (const cx<T>*)c_in, (const T*)ytab, bs.thr32,      \
-          bs.nb, bs.hist_copies, bs.turns, bs.thr_lds, partial, (const cx<T>*)tw, frame, tiles_dev, ntiles); \
-    };                                                                                                       \
-    if (basis == 1) run(k_xpost<T, NV, true>); else run(k_xpost<T, NV, false>);                              \
+    constexpr int TP = PostShape<T, NV>::TP;                                                                 \
+    if (lines < TP) return launch_xpost_few<T>(fs, PKM_POST_ARGS);                                           \
+    if (lines > TP) return hipErrorInvalidValue;                                                             \
+    post_run<T, NV, true>(PKM_POST_ARGS);                                                                    \
     break;                                                                                                   \
   }
   switch (fs.n) { PKM_FOR_SIDES(PKM_POST_SIDE) default: return hipErrorInvalidValue; }
@@ -333,10 +356,31 @@ hipError_t launch_xpost(const FftShape& fs, int nrecs, const FieldRec* recs_dev,
   return hipGetLastError();
 }
 
+// Blocks of fewer lines than the side's own (checked by launch_xpost); sources of their own, which compile
+// beside the others.
+template <typename T>
+hipError_t launch_xpost_few(const FftShape& fs, int lines, int nrecs, const FieldRec* recs_dev, int nslots,
+                            int with_l0, const void* c_in, const void* ytab, const BinSpec& bs, double kf,
+                            double* partial, int nblocks, const void* tw, const Frame& frame, int basis,
+                            const unsigned* tiles_dev, int ntiles, hipStream_t s) {
+#define PKM_POST_SIDE(NV)                                                                                    \
+  case NV:                                                                                                   \
+    if constexpr (PostShape<T, NV>::TP > 1) {                                                                \
+      post_run<T, NV, false>(PKM_POST_ARGS);                                                                 \
+      return hipGetLastError();                                                                              \
+    }                                                                                                        \
+    return hipErrorInvalidValue;
+  switch (fs.n) { PKM_FOR_SIDES(PKM_POST_SIDE) default: return hipErrorInvalidValue; }
+#undef PKM_POST_SIDE
+}
+
+#define PKM_POST_PARAMS                                                                                       \
+  const FftShape&, int, int, const FieldRec*, int, int, const void*, const void*, const BinSpec&, double,     \
+      double*, int, const void*, const Frame&, int, const unsigned*, int, hipStream_t
 #define PKM_POST_INST(T)                                                                                      \
-  template bool post_geometry<T>(int, PostGeometry*);                                                         \
-  template hipError_t launch_xpost<T>(const FftShape&, int, const FieldRec*, int, int, const void*,           \
-                                      const void*, const BinSpec&, double, double*, int, const void*,         \
-                                      const Frame&, int, const unsigned*, int, hipStream_t);
+  extern template hipError_t launch_xpost_few<T>(PKM_POST_PARAMS);                                            \
+  template bool post_geometry<T>(int, int, PostGeometry*);                                                    \
+  template hipError_t launch_xpost<T>(PKM_POST_PARAMS);
+#define PKM_POST_FEW_INST(T) template hipError_t launch_xpost_few<T>(PKM_POST_PARAMS);
 
 }  // namespace pkm

@@ -45,13 +45,14 @@ struct FieldRec {
 size_t zpass_smem_bytes(const FftShape& fs, bool fp64);
 size_t colpass_smem_bytes(const FftShape& fs, bool fp64);
 
-// The post-pass of a side: kz lines per tile, threads per block, persistent blocks per CU and LDS
-// bytes without histograms and thresholds.  false: no such side.
+// The post-pass of a side with blocks of `lines` kz lines (0, or more than the side's own: those): lines per
+// tile, threads per block, persistent blocks per CU that the registers leave room for, and LDS bytes without
+// histograms and thresholds.  false: no such side.
 struct PostGeometry {
   int tp, threads, per_cu;
   size_t smem;
 };
-template <typename T> bool post_geometry(int n, PostGeometry* g);
+template <typename T> bool post_geometry(int n, int lines, PostGeometry* g);
 
 // Orthogonal matrix (rows r[0..2], r[3..5], r[6..8]) applied to every unit vector, node
 // direction and wave vector alike, before harmonics or monomials are evaluated.  The sums
@@ -154,17 +155,22 @@ hipError_t launch_zpre(const FftShape& fs, const void* g_in, const T* real_in, i
                        const void* tw, const Frame& frame, int basis, int kz_live, hipStream_t s);
 
 // Last transform pass of every field of the group (along y), sum over m of Y_lm(khat) B_lm per
-// multipole slot, product with C and binning over the listed tiles (x << 16 | kz0).  Odd l
+// multipole slot, product with C and binning over the listed tiles (x << 16 | kz0) of `lines` kz lines.  Odd l
 // (spherical basis) are binned as Im[C conj (sum)] instead of Re.  Lines come slot by slot, |m|
 // ascending within a slot.  Per block the partial sums are rows of nb bins:
 // [count, sum |k|, sum |C|^2] when with_l0, then one row of sum 4 pi Y Re[C conj B] per slot.
 // basis 1: the slot sums (p!/a!) khat^a B_a over the monomials a of one degree p, and its row
 // holds sum Re[C conj (that sum)] without the 4 pi.
 template <typename T>
-hipError_t launch_xpost(const FftShape& fs, int nrecs, const FieldRec* recs_dev, int nslots, int with_l0,
+hipError_t launch_xpost(const FftShape& fs, int lines, int nrecs, const FieldRec* recs_dev, int nslots, int with_l0,
                         const void* c_in, const void* ytab, const BinSpec& bs, double kf,
                         double* partial, int nblocks, const void* tw, const Frame& frame, int basis,
                         const unsigned* tiles_dev, int ntiles, hipStream_t s);
+template <typename T>
+hipError_t launch_xpost_few(const FftShape& fs, int lines, int nrecs, const FieldRec* recs_dev, int nslots, int with_l0,
+                            const void* c_in, const void* ytab, const BinSpec& bs, double kf,
+                            double* partial, int nblocks, const void* tw, const Frame& frame, int basis,
+                            const unsigned* tiles_dev, int ntiles, hipStream_t s);
 
 // out[map[v]] (+)= sum_b partial[b*nvals + v] (map null -> identity), fixed order.
 hipError_t launch_reduce(const double* partial, int nblocks, int nvals, double* out, const int* map, int accumulate,

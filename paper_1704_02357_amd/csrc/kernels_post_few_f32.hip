@@ -1,0 +1,6 @@
+// Post-pass of the weighted fields in blocks of fewer lines, float.
+#include "fields_post.hpp"
+
+namespace pkm {
+PKM_POST_FEW_INST(float)
+}  // namespace pkm

@@ -46,7 +46,8 @@ struct ComputeCfg {
   std::vector<GroupCfg> groups;
   // what the last k edge leaves of the spectrum: |n|^2 below tmax, so many kz planes of a field buffer
   // and post-pass tiles
-  int tmax = 0, kz_live = 0, ntiles = 0, post_blocks = 1, thr_lds = 1;
+  int tmax = 0, kz_live = 0, ntiles = 0, post_blocks = 1;
+  int lines = 1, thr_lds = 1;  // kz lines of a post-pass block; whether it stages the k thresholds
 };
 
 struct pkm_plan {
@@ -359,10 +360,27 @@ size_t field_bytes(int n, bool fp64) {
                                  : sizeof(float2) * field_plane_stride<float>(n));
 }
 
-PostGeometry post_geometry_of(int n, bool fp64) {
+PostGeometry post_geometry_of(int n, bool fp64, int lines = 0) {
   PostGeometry g{};
-  if (fp64) (void)post_geometry<double>(n, &g); else (void)post_geometry<float>(n, &g);
+  if (fp64) (void)post_geometry<double>(n, lines, &g); else (void)post_geometry<float>(n, lines, &g);
   return g;
+}
+
+// The post-pass of a request whose largest group has `nv` histogram values, in FP64, and n_edges thresholds:
+// the side's own blocks where one histogram and the thresholds fit beside their lines in the LDS of a CU, else
+// the most lines that leave room (a line of FP64 192^3 takes 6.9 KB: 1300 bins of l <= 4 leave room for 15 of
+// 16).  When not even one line does, the thresholds stay in global memory; false: no room then either.
+constexpr size_t CU_LDS = 160 * 1024;
+bool fit_post(int n, bool fp64, size_t nv, size_t n_edges, PostGeometry* geo, int* thr_lds) {
+  const size_t hist = sizeof(double) * nv, thr = sizeof(int) * n_edges;
+  *thr_lds = 1;
+  *geo = post_geometry_of(n, fp64);
+  while (geo->tp > 1 && geo->smem + hist + thr > CU_LDS) {
+    *geo = post_geometry_of(n, fp64, geo->tp - 1);
+    geo->per_cu = 1;  // (its LDS is full but for less than a line)
+  }
+  if (geo->smem + hist + thr > CU_LDS) *thr_lds = 0;
+  return geo->smem + hist + (*thr_lds ? thr : 0) <= CU_LDS;
 }
 
 // Persistent post-pass blocks for a number of tiles: as many as the registers leave room for, in
@@ -374,7 +392,8 @@ int post_blocks_for(const PostGeometry& g, int cus, int ntiles) {
 
 // LDS base of the limit on k bins: a request is refused when this, the thresholds and five rows of one
 // histogram exceed the LDS of a CU, and a deterministic one when its histograms exceed 150 KB with one
-// per wavefront of tile_post lines of e_post elements per thread.  The kernels need less.
+// per wavefront of tile_post lines of e_post elements per thread.  What the kernels take is another matter:
+// fit_post chooses blocks that fit.
 size_t bin_limit_base(const FftShape& fs, bool fp64) {
   const size_t n = fs.n;
   return (fp64 ? sizeof(double2) : sizeof(float2)) * (fs.tile_post * (n + n / 8 + 1) + fs.tile_post * n + n);
@@ -633,27 +652,6 @@ void prepare_compute(pkm_plan* pl, int ell_max, const double* k_edges, int n_edg
   std::vector<int> thr32(n_edges);
   for (int i = 0; i < n_edges; ++i) thr32[i] = (int)std::min<long long>(thr[i], 1 << 30);
   check_hip(pl, hipMemcpy(pl->thr_dev, thr32.data(), sizeof(int) * n_edges, hipMemcpyHostToDevice), "thr");
-  // the part of the spectrum below the last edge: post-pass tiles (x, kz0), x-major
-  const PostGeometry geo = post_geometry_of(n, pl->fp64);
-  cc.tmax = thr32[nb];
-  std::vector<unsigned> tiles;
-  for (int x = 0; x < n; ++x) {
-    if (x == n / 2) continue;
-    const int fx = x < n / 2 ? x : x - n;
-    for (int kz0 = 0; kz0 < n / 2 && fx * fx + kz0 * kz0 < cc.tmax; kz0 += geo.tp) {
-      tiles.push_back((unsigned)x << 16 | (unsigned)kz0);
-      cc.kz_live = std::max(cc.kz_live, std::min(kz0 + geo.tp, n / 2));
-    }
-  }
-  cc.ntiles = (int)tiles.size();
-  cc.post_blocks = post_blocks_for(geo, pl->fs.cus, cc.ntiles);
-  if (pl->tiles_cap < cc.ntiles) {
-    dfree(pl, pl->tiles_dev);
-    pl->tiles_dev = (unsigned*)dalloc(pl, sizeof(unsigned) * tiles.size());
-    pl->tiles_cap = cc.ntiles;
-  }
-  if (cc.ntiles)
-    check_hip(pl, hipMemcpy(pl->tiles_dev, tiles.data(), sizeof(unsigned) * tiles.size(), hipMemcpyHostToDevice), "tiles");
   // fields and groups
   struct F { int l, m, slot; };
   std::vector<std::vector<F>> groups;
@@ -690,10 +688,36 @@ void prepare_compute(pkm_plan* pl, int ell_max, const double* k_edges, int n_edg
   }
   const int rows = 2 + ell_rows(ell_max, basis);  // count, ksum, Q0, then Q2, Q4, ... (or Q1, Q2, ...)
   const size_t col_lds = bin_limit_base(pl->fs, sizeof(T) == 8) + sizeof(long long) * (size_t)n_edges;
-  if (col_lds + sizeof(double) * 5 * (size_t)nb > 160 * 1024) {
+  size_t most_slots = 0;  // (the first group carries three rows more)
+  for (size_t gi = 0; gi < groups.size(); ++gi)
+    most_slots = std::max<size_t>(most_slots, (groups[gi].empty() ? 0 : groups[gi].back().slot + 1) + (gi == 0 ? 3 : 0));
+  PostGeometry geo{};
+  if (col_lds + sizeof(double) * 5 * (size_t)nb > CU_LDS ||
+      !fit_post(n, sizeof(T) == 8, most_slots * nb, n_edges, &geo, &cc.thr_lds)) {
     pl->err = "too many k bins for one pass";
     throw Fail{PKM_EINVAL};
   }
+  cc.lines = geo.tp;
+  // the part of the spectrum below the last edge: post-pass tiles (x, kz0), x-major
+  cc.tmax = thr32[nb];
+  std::vector<unsigned> tiles;
+  for (int x = 0; x < n; ++x) {
+    if (x == n / 2) continue;
+    const int fx = x < n / 2 ? x : x - n;
+    for (int kz0 = 0; kz0 < n / 2 && fx * fx + kz0 * kz0 < cc.tmax; kz0 += geo.tp) {
+      tiles.push_back((unsigned)x << 16 | (unsigned)kz0);
+      cc.kz_live = std::max(cc.kz_live, std::min(kz0 + geo.tp, n / 2));
+    }
+  }
+  cc.ntiles = (int)tiles.size();
+  cc.post_blocks = post_blocks_for(geo, pl->fs.cus, cc.ntiles);
+  if (pl->tiles_cap < cc.ntiles) {
+    dfree(pl, pl->tiles_dev);
+    pl->tiles_dev = (unsigned*)dalloc(pl, sizeof(unsigned) * tiles.size());
+    pl->tiles_cap = cc.ntiles;
+  }
+  if (cc.ntiles)
+    check_hip(pl, hipMemcpy(pl->tiles_dev, tiles.data(), sizeof(unsigned) * tiles.size(), hipMemcpyHostToDevice), "tiles");
   const int total_vals = rows * nb;
   if (pl->out_cap < (size_t)total_vals) {
     dfree(pl, pl->out_dev);
@@ -773,8 +797,7 @@ void prepare_compute(pkm_plan* pl, int ell_max, const double* k_edges, int n_edg
   // Histograms: one per wavefront when the LDS of the resident blocks allows; else wavefronts take turns
   // on a copy, so that the sums never depend on scheduling.
   const int waves = (geo.threads + 63) / 64;
-  const size_t lds = 160 * 1024;
-  cc.thr_lds = geo.smem + sizeof(int) * (size_t)n_edges + sizeof(double) * (size_t)max_nv <= lds;
+  const size_t lds = CU_LDS;
   const size_t fixed = geo.smem + (cc.thr_lds ? sizeof(int) * (size_t)n_edges : 0) + 512;
   const size_t budget = lds / geo.per_cu > fixed ? lds / geo.per_cu - fixed : 0;
   for (auto& gc : cc.groups) {
@@ -826,7 +849,7 @@ template <typename T> void enqueue_compute(pkm_plan* pl) {
     }
     {
       StageScope ss(pl, PKM_STAGE_XPOST);
-      check_hip(pl, launch_xpost<T>(pl->fs, gc.nf, pl->ftab_dev + gc.pofs, gc.nslots, gi == 0 ? 1 : 0,
+      check_hip(pl, launch_xpost<T>(pl->fs, cc.lines, gc.nf, pl->ftab_dev + gc.pofs, gc.nslots, gi == 0 ? 1 : 0,
                                     pl->c, pl->ytab,
                                     BinSpec{nullptr, pl->thr_dev, cc.nb, gc.copies, gc.turns, cc.thr_lds},
                                     (double)(2.0 * M_PI / pl->p.box_len), pl->partial, cc.post_blocks, pl->tw,
