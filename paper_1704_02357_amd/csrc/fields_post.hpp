@@ -44,14 +44,14 @@ template <typename T, int N> struct PostShape {
   }
 };
 
-// Tiles of a persistent post-pass block.  When the tile count and the grid are multiples of
-// 8, block b (dispatched to XCD b mod 8) walks a contiguous eighth of the tiles, so the
-// blocks of one XCD work on neighbouring tiles at the same time.
+// Tiles of a persistent post-pass block.  When the grid is a multiple of 8, block b (dispatched to XCD
+// b mod 8) walks a contiguous eighth of the tiles, so the blocks of one XCD work on neighbouring tiles at the
+// same time; a block may find none left.
 struct TileWalk {
   int first, step, end, chunk0;
   __device__ TileWalk(int nt) {
     const int G = gridDim.x, b = blockIdx.x;
-    if (G % 8 == 0 && G <= nt) {
+    if (G % 8 == 0) {
       const int x = b % 8;
       chunk0 = (int)((long long)nt * x / 8);
       first = b / 8;

@@ -73,3 +73,29 @@ def test_bin_limit_of_the_default_shape(gpu, n, prec, most):
     with pytest.raises(PkmError, match="too many k bins"):
         plan.prepare(4, _edges(n, most + 1), 100)
     plan.close()
+
+
+@pytest.mark.parametrize("prec", [1, 0])
+@pytest.mark.parametrize("n,top", [(16, 1.2), (16, 3.3), (64, 2.5), (1024, 1.2)])
+def test_few_modes_equal_direct_sums(gpu, n, top, prec):
+    """Last edges of a few fundamental modes: fewer post-pass tiles than XCDs."""
+    from oracle.direct import shell_modes, yamamoto_at_modes
+    from oracle.estimator import default_params
+    from paper_1704_02357_amd import Plan
+    from tests.test_gpu_sizes import _cube_catalog
+    box = 4.0 * n
+    obs = (0.13 * box, -0.21 * box, -1.7 * box)
+    cat = _cube_catalog(n, box, 12, seed=n)
+    thr = np.array([1, math.ceil(top * top)], dtype=np.int64)
+    edges = 2 * math.pi / box * np.sqrt(thr - 0.5)
+    params = default_params(n, box, observer=obs, window=1, interlaced=False, compensated=True)
+    modes, b = shell_modes(n, thr, [0])
+    poles, counts, kmean = yamamoto_at_modes(cat, None, params, [0, 2], modes, b, 1)
+    print(f"[case] few modes side {n} top {top} prec={prec}", flush=True)
+    plan = Plan(n, box, observer=obs, window=1, interlaced=False, compensated=True, precision=prec, ell_max_hint=2)
+    plan.paint(cat)
+    got = plan.compute_multipoles(2, edges)
+    plan.close()
+    ref = {"poles": poles, "n_modes": counts.astype(np.int64), "k_mean": kmean, "alpha": 0.0,
+           "norm_I": got["norm_I"], "shot_noise": got["shot_noise"]}
+    assert_pole_parity(dict(got, alpha=0.0), ref, prec, f"side {n} top {top}")
