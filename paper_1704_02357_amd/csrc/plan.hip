@@ -34,7 +34,8 @@ using namespace pkm;
 // One field group of a multipole request: its pre-pass entries and post-pass lines in the field
 // tables, reduce map, histogram shape.
 struct GroupCfg {
-  int nf = 0, fofs = 0, nent = 0, pofs = 0, mofs = 0, nv = 0, nslots = 0, copies = 1, turns = 1;
+  int nf = 0, fofs = 0, nent = 0, pofs = 0, mofs = 0, nv = 0, nslots = 0, copies = 1, turns = 1, blocks = 1;
+  int thr_lds = 1;  // the post-pass stages the k thresholds in LDS
 };
 struct ComputeCfg {
   int ell_max = -1;
@@ -46,8 +47,8 @@ struct ComputeCfg {
   std::vector<GroupCfg> groups;
   // what the last k edge leaves of the spectrum: |n|^2 below tmax, so many kz planes of a field buffer
   // and post-pass tiles
-  int tmax = 0, kz_live = 0, ntiles = 0, post_blocks = 1;
-  int lines = 1, thr_lds = 1;  // kz lines of a post-pass block; whether it stages the k thresholds
+  int tmax = 0, kz_live = 0, ntiles = 0;
+  int lines = 1;  // kz lines of a post-pass block
 };
 
 struct pkm_plan {
@@ -375,20 +376,17 @@ bool fit_post(int n, bool fp64, size_t nv, size_t n_edges, PostGeometry* geo, in
   const size_t hist = sizeof(double) * nv, thr = sizeof(int) * n_edges;
   *thr_lds = 1;
   *geo = post_geometry_of(n, fp64);
-  while (geo->tp > 1 && geo->smem + hist + thr > CU_LDS) {
-    *geo = post_geometry_of(n, fp64, geo->tp - 1);
-    geo->per_cu = 1;  // (its LDS is full but for less than a line)
-  }
+  while (geo->tp > 1 && geo->smem + hist + thr > CU_LDS) *geo = post_geometry_of(n, fp64, geo->tp - 1);
   if (geo->smem + hist + thr > CU_LDS) *thr_lds = 0;
   return geo->smem + hist + (*thr_lds ? thr : 0) <= CU_LDS;
 }
 
-// Persistent post-pass blocks for a number of tiles: as many as the registers leave room for, or as there are
-// tiles, in multiples of 8 (one share of the tiles per XCD).  Few tiles are rounded up: with 216 blocks for the
-// 222 tiles of 64^3, six of them took two tiles one after the other and the pass nearly twice the time (152
-// fields of l <= 16 in FP32: 259 -> 139 us; 128^3, 1656 blocks for 1658 tiles: 384 -> 248 us).
-int post_blocks_for(const PostGeometry& g, int cus, int ntiles) {
-  const int most = g.per_cu * (cus > 0 ? cus : 256);
+// Persistent post-pass blocks for a number of tiles: per_cu a CU, or as many as there are tiles, in multiples of
+// 8 (one share of the tiles per XCD).  Few tiles are rounded up: with 216 blocks for the 222 tiles of 64^3, six
+// of them took two tiles one after the other and the pass nearly twice the time (152 fields of l <= 16 in FP32:
+// 259 -> 139 us; 128^3, 1656 blocks for 1658 tiles: 384 -> 248 us).
+int post_blocks_for(int per_cu, int cus, int ntiles) {
+  const int most = per_cu * (cus > 0 ? cus : 256);
   return ntiles == 0 ? 1 : std::min((ntiles + 7) / 8 * 8, std::max(8, most / 8 * 8));
 }
 
@@ -694,8 +692,9 @@ void prepare_compute(pkm_plan* pl, int ell_max, const double* k_edges, int n_edg
   for (size_t gi = 0; gi < groups.size(); ++gi)
     most_slots = std::max<size_t>(most_slots, (groups[gi].empty() ? 0 : groups[gi].back().slot + 1) + (gi == 0 ? 3 : 0));
   PostGeometry geo{};
+  int thr_lds = 1;
   if (col_lds + sizeof(double) * 5 * (size_t)nb > CU_LDS ||
-      !fit_post(n, sizeof(T) == 8, most_slots * nb, n_edges, &geo, &cc.thr_lds)) {
+      !fit_post(n, sizeof(T) == 8, most_slots * nb, n_edges, &geo, &thr_lds)) {
     pl->err = "too many k bins for one pass";
     throw Fail{PKM_EINVAL};
   }
@@ -712,7 +711,6 @@ void prepare_compute(pkm_plan* pl, int ell_max, const double* k_edges, int n_edg
     }
   }
   cc.ntiles = (int)tiles.size();
-  cc.post_blocks = post_blocks_for(geo, pl->fs.cus, cc.ntiles);
   if (pl->tiles_cap < cc.ntiles) {
     dfree(pl, pl->tiles_dev);
     pl->tiles_dev = (unsigned*)dalloc(pl, sizeof(unsigned) * tiles.size());
@@ -788,25 +786,28 @@ void prepare_compute(pkm_plan* pl, int ell_max, const double* k_edges, int n_edg
     pl->map_cap = (int)maps.size();
   }
   check_hip(pl, hipMemcpy(pl->map_dev, maps.data(), sizeof(int) * maps.size(), hipMemcpyHostToDevice), "maps");
-  const int nblk = cc.post_blocks;
-  int max_nv = 0;
-  for (auto& gc : cc.groups) max_nv = std::max(max_nv, gc.nv);
-  if (pl->partial_cap < (size_t)nblk * max_nv) {
-    dfree(pl, pl->partial);
-    pl->partial = (double*)dalloc(pl, sizeof(double) * (size_t)nblk * max_nv);
-    pl->partial_cap = (size_t)nblk * max_nv;
-  }
   // Histograms: one per wavefront when the LDS of the resident blocks allows; else wavefronts take turns
-  // on a copy, so that the sums never depend on scheduling.
+  // on a copy, so that the sums never depend on scheduling.  The resident blocks are those that registers and
+  // LDS, in units of 1280 bytes, leave room for with one histogram each.  A block that the thresholds alone keep
+  // from sharing its CU leaves them in global memory (1024^3 FP32, 107 bins of l <= 8: 258.6 ms an estimate with
+  // one block a CU, 253.8 with two).  Blocks that wait for LDS only add histograms to clear, write and reduce
+  // (1000 bins at 128^3 in FP32: post-pass and reduction 198 us with 1656 blocks, 119 with the 768 that fit).
   const int waves = (geo.threads + 63) / 64;
-  const size_t lds = CU_LDS;
-  const size_t fixed = geo.smem + (cc.thr_lds ? sizeof(int) * (size_t)n_edges : 0) + 512;
-  const size_t budget = lds / geo.per_cu > fixed ? lds / geo.per_cu - fixed : 0;
+  size_t partials = 0;
   for (auto& gc : cc.groups) {
-    const size_t row = sizeof(double) * (size_t)std::max(1, gc.nv);
-    const int copies = std::max(1, (int)std::min<size_t>((size_t)waves, budget / row));
+    const size_t row = sizeof(double) * (size_t)std::max(1, gc.nv), thr = sizeof(int) * (size_t)n_edges;
+    auto fitting = [&](size_t bytes) {
+      return std::max(1, (int)std::min<size_t>(geo.per_cu, CU_LDS / ((bytes + 1279) / 1280 * 1280)));
+    };
+    gc.thr_lds = thr_lds && !(fitting(geo.smem + thr + row) == 1 && fitting(geo.smem + row) > 1);
+    const size_t fixed = geo.smem + (gc.thr_lds ? thr : 0);
+    const int per_cu = fitting(fixed + row);
+    const size_t room = CU_LDS / per_cu / 1280 * 1280;
+    const int copies = std::max(1, (int)std::min<size_t>((size_t)waves, room > fixed ? (room - fixed) / row : 0));
     gc.turns = (waves + copies - 1) / copies;
     gc.copies = (waves + gc.turns - 1) / gc.turns;
+    gc.blocks = post_blocks_for(per_cu, pl->fs.cus, cc.ntiles);
+    partials = std::max(partials, (size_t)gc.blocks * gc.nv);
     if (pl->p.deterministic) {
       const int w = ((n / pl->fs.e_post) * pl->fs.tile_post + 63) / 64;
       const size_t left = col_lds + 1024 < 150 * 1024 ? 150 * 1024 - col_lds - 1024 : 0;
@@ -815,6 +816,11 @@ void prepare_compute(pkm_plan* pl, int ell_max, const double* k_edges, int n_edg
         throw Fail{PKM_ENOMEM};
       }
     }
+  }
+  if (pl->partial_cap < partials) {
+    dfree(pl, pl->partial);
+    pl->partial = (double*)dalloc(pl, sizeof(double) * partials);
+    pl->partial_cap = partials;
   }
   cc.ell_max = ell_max;
   cc.basis = basis;
@@ -853,13 +859,13 @@ template <typename T> void enqueue_compute(pkm_plan* pl) {
       StageScope ss(pl, PKM_STAGE_XPOST);
       check_hip(pl, launch_xpost<T>(pl->fs, cc.lines, gc.nf, pl->ftab_dev + gc.pofs, gc.nslots, gi == 0 ? 1 : 0,
                                     pl->c, pl->ytab,
-                                    BinSpec{nullptr, pl->thr_dev, cc.nb, gc.copies, gc.turns, cc.thr_lds},
-                                    (double)(2.0 * M_PI / pl->p.box_len), pl->partial, cc.post_blocks, pl->tw,
+                                    BinSpec{nullptr, pl->thr_dev, cc.nb, gc.copies, gc.turns, gc.thr_lds},
+                                    (double)(2.0 * M_PI / pl->p.box_len), pl->partial, gc.blocks, pl->tw,
                                     pl->frame, cc.basis, pl->tiles_dev, cc.ntiles, s),
                 "post-pass");
     }
     StageScope ss(pl, PKM_STAGE_REDUCE);
-    check_hip(pl, launch_reduce(pl->partial, cc.post_blocks, gc.nv, pl->out_dev, pl->map_dev + gc.mofs, 1, s), "reduce");
+    check_hip(pl, launch_reduce(pl->partial, gc.blocks, gc.nv, pl->out_dev, pl->map_dev + gc.mofs, 1, s), "reduce");
   }
 }
 
@@ -1449,7 +1455,7 @@ int64_t footprint(const pkm_params* p, int ell_max, int n_edges, int64_t n_parti
   const int64_t nb = std::max(1, n_edges - 1);
   const PostGeometry geo = post_geometry_of(p->nmesh, p->precision == PKM_FP64);
   const int tiles = p->nmesh * ((p->nmesh / 2 + geo.tp - 1) / geo.tp);
-  const int64_t partial = (int64_t)post_blocks_for(geo, 0, tiles) * (3 + ell_max / 2) * nb * 8;
+  const int64_t partial = (int64_t)post_blocks_for(geo.per_cu, 0, tiles) * (3 + ell_max / 2) * nb * 8;
   const int64_t ts = 8;
   const int64_t ntiles = (n / ts) * (n / ts) * (n / ts);
   const int64_t det = p->deterministic ? 8 * n * n * n * (p->interlaced ? 2 : 1) : 0;

@@ -44,6 +44,7 @@ def test_many_bins_equal_oracle(gpu, n, prec, ell, nb, shape):
     (144, 1, 4, 3150), (192, 1, 4, 1300), (192, 1, 4, 2250), (288, 1, 4, 2900), (192, 0, 4, 2830), (768, 0, 4, 3000),
     (1024, 0, 4, 2500),
     (432, 1, 8, 2460),  # seven rows: the thresholds stay in global memory
+    (1024, 0, 4, 107),  # so that two blocks share a CU: likewise
 ])
 def test_many_bins_equal_coarse_bins(gpu, n, prec, ell, nb):
     from paper_1704_02357_amd import Plan
