@@ -538,14 +538,20 @@ __device__ __forceinline__ void monomial_eval(int p, int code, T coef, DIR dir, 
   const int i = code >> 5, j = code & 31;
 #pragma unroll
   for (int v = 0; v < NV; ++v) out[v] = coef;
-  for (int q = 0; q < p; ++q) {
+  // (a loop per axis: p is uniform, and one loop choosing the factor would take two selects a point and factor)
+  auto times = [&](int count, auto pick) {
+    for (int q = 0; q < count; ++q) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      T x, y, z;
-      dir(v, x, y, z);
-      out[v] *= q < i ? x : q < i + j ? y : z;
+      for (int v = 0; v < NV; ++v) {
+        T x, y, z;
+        dir(v, x, y, z);
+        out[v] *= pick(x, y, z);
+      }
     }
-  }
+  };
+  times(i, [](T x, T, T) { return x; });
+  times(j, [](T, T y, T) { return y; });
+  times(p - i - j, [](T, T, T z) { return z; });
 }
 
 // p! / (i! j! (p-i-j)!), exact in integers for p <= 16 (at most 2018016)

@@ -205,11 +205,26 @@ __global__ void __launch_bounds__((PostShape<T, N>::THREADS), (PostShape<T, N>::
     const T a0 = (T)(frm.r[0] * fx + frm.r[2] * kz), a1 = (T)(frm.r[3] * fx + frm.r[5] * kz),
             a2 = (T)(frm.r[6] * fx + frm.r[8] * kz);
     const T tf = (T)t;
-    auto dir = [&](int e, T& vx, T& vy, T& vz) {
-      const T fy = (S::TIGHT ? fresh(tf) : tf) + (T)(PT * e - (e >= E / 2 ? N : 0));
+    auto form = [&](int e, T& vx, T& vy, T& vz) {
+      const T fy = (S::TIGHT && !CART ? fresh(tf) : tf) + (T)(PT * e - (e >= E / 2 ? N : 0));
       vx = (a0 + frm.at<T>(1) * fy) * ki[e];
       vy = (a1 + frm.at<T>(4) * fy) * ki[e];
       vz = (a2 + frm.at<T>(7) * fy) * ki[e];
+    };
+    // (the monomials take every component several times, and have no recurrence state: theirs are kept)
+    T ud[CART ? E : 1][3];
+    if constexpr (CART) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) form(e, ud[e][0], ud[e][1], ud[e][2]);
+    }
+    auto dir = [&](int e, T& vx, T& vy, T& vz) {
+      if constexpr (CART) {
+        vx = ud[e][0];
+        vy = ud[e][1];
+        vz = ud[e][2];
+      } else {
+        form(e, vx, vy, vz);
+      }
     };
     __syncthreads();  // C staged
     const unsigned tl_next = tiles[walk.tile(j + walk.step < walk.end ? j + walk.step : j)];
