@@ -4,6 +4,7 @@
 // any other IEEE implementation of the same formula bit for bit.
 #include <algorithm>
 
+#include "../../include/pkm.h"
 #include "kernels.hpp"
 #include "device_common.hpp"
 
@@ -513,6 +514,16 @@ __device__ __forceinline__ void flush_column(const double* __restrict__ reg, int
   }
 }
 
+// Units of work of a painting block: each of its particles on each mesh, or (`parts` then has them) in slabs.
+// All of PKM_MAX_PARTICLES may lie in one tile (a 16^3 mesh is one): twice that, and a step of the block's
+// threads beyond, fit 32 bits only without a sign.
+__host__ __device__ constexpr unsigned paint_units(int begin, int end, int parts) {
+  return (unsigned)(end - begin) * (unsigned)parts;
+}
+static_assert((long long)paint_units(0, (int)PKM_MAX_PARTICLES, 2) == 2 * PKM_MAX_PARTICLES &&
+                  2 * PKM_MAX_PARTICLES + 1024 < 1ll << 32,
+              "a painting block's units must not wrap");
+
 // A painting block takes ZT consecutive tiles of a row along z, whose particles are consecutive too.
 template <int W, int TS, int ZT> struct PaintShape {
   using R = PaintReach<W>;
@@ -552,10 +563,10 @@ __global__ void __launch_bounds__((PaintShape<W, TS, ZT>::THREADS))
   // 52 to 43 us).
   const bool fine = (end - start) < (int)blockDim.x / 2;
   const int parts = (two ? 2 : 1) * (fine ? W : 1);
-  const int units = (end - start) * parts;
+  const unsigned units = paint_units(start, end, parts);
   // (a thread's particle is fetched one unit ahead, the first one while the regions are cleared)
   double4 next = make_double4(0.0, 0.0, 0.0, 0.0);
-  if (!fine && (int)threadIdx.x < units) next = payload[start + ((int)threadIdx.x >> two)];
+  if (!fine && threadIdx.x < units) next = payload[start + (threadIdx.x >> two)];
   const int ncells = S::CELLS1 + (two ? S::CELLS2 : 0);
   for (int i = threadIdx.x; i < (ncells + 1) / 2; i += blockDim.x)
     reinterpret_cast<double2*>(smem)[i] = make_double2(0.0, 0.0);
@@ -607,16 +618,16 @@ __global__ void __launch_bounds__((PaintShape<W, TS, ZT>::THREADS))
                              wsc, nmesh, rel, second ? n2 : n1, second ? z2 : z1, isc, a0, a1);
   };
   if (fine) {
-    for (int j = threadIdx.x; j < units; j += blockDim.x) {
+    for (int j = threadIdx.x; j < (int)units; j += blockDim.x) {
       const int q = two ? j / (2 * W) : j / W, sub = j - q * parts;
       const bool second = sub >= W;
       const int a0 = second ? sub - W : sub;
       paint_unit(payload[start + q], second, a0, a0 + 1);
     }
   } else {
-    for (int j = threadIdx.x; j < units; j += blockDim.x) {
+    for (unsigned j = threadIdx.x; j < units; j += blockDim.x) {
       const double4 p = next;
-      if (j + (int)blockDim.x < units) next = payload[start + ((j + (int)blockDim.x) >> two)];
+      if (j + blockDim.x < units) next = payload[start + ((j + blockDim.x) >> two)];
       paint_unit(p, two && (j & 1), 0, W);
     }
   }
