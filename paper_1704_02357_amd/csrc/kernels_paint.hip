@@ -405,7 +405,7 @@ template <int W> __device__ __forceinline__ double taps(double u, double* wt) {
 // The pass is bound by vector instructions, a third of which were the conversion to 64 bits, so a b is
 // split by two fused adds instead: adding 3 2^83 rounds it to a multiple of 2^32 whose quotient is the low
 // word of the sum, and adding 3 2^51 to the rest, |rest| <= 2^31, leaves that as a 64-bit integer above the
-// constant's own bits.  For |a b| <= 2^61 (callers leave out NaN and infinities).
+// constant's own bits.  For |a b| < 2^63 (callers leave out NaN and infinities).
 __device__ __forceinline__ long long fixed_product(double a, double b) {
   constexpr double HI = 0x1.8p84, LO = 0x1.8p52;
   const double h = fma(a, b, HI);
@@ -573,8 +573,10 @@ __global__ void __launch_bounds__((PaintShape<W, TS, ZT>::THREADS))
   const int tz = tile % tpa, ty = (tile / tpa) % tpa, tx = tile / (tpa * tpa);
   const int t0[3] = {tx * ts, ty * ts, tz * ts};
   // fixed-point scale (FP32 meshes): no region cell can exceed B = (particles that reach it: those of
-  // two neighbouring tiles of the row, at most) x (largest |payload weight|), since a particle's taps sum to its
-  // weight; B sc <= 2^61
+  // two neighbouring tiles of the row, or all of the block's where only their sum is known) x (largest
+  // |payload weight|), since a particle's taps sum to its weight.  B (1 + 2^-20) sc <= 2^63: all 63 bits, less
+  // room for half a unit of rounding a particle, so that a block of four tiles has no coarser sums than
+  // one-tile blocks with B sc <= 2^61.
   double sc = 1.0;
   if constexpr (DET) {
     sc = *gsc;
@@ -584,8 +586,8 @@ __global__ void __launch_bounds__((PaintShape<W, TS, ZT>::THREADS))
     const double wm = fmax(*wmax_d, wmax_r ? alpha * *wmax_r : 0.0);
     const double bound = (double)most * wm;
     int e = 0;
-    if (bound > 0.0) (void)frexp(bound, &e);  // bound < 2^e
-    sc = ldexp(1.0, 61 - e);
+    if (bound > 0.0) (void)frexp(bound * (1.0 + 0x1p-20), &e);  // bound (1 + 2^-20) < 2^e
+    sc = ldexp(1.0, 63 - e);
   }
   const double isc = 1.0 / sc;  // a power of two: exact
   __syncthreads();
@@ -598,7 +600,7 @@ __global__ void __launch_bounds__((PaintShape<W, TS, ZT>::THREADS))
     int rel[3];
     const double wsc = p.w * sc;
     if constexpr (sizeof(T) == 4 || DET) {  // (taps that are not numbers count as nothing)
-      if (!(fabs(wsc) <= 0x1p62)) return;
+      if (!(fabs(wsc) <= 0x1p63)) return;
       if (W > 1 && !(fabs(u[0]) + fabs(u[1]) + fabs(u[2]) < __builtin_huge_val())) return;
     }
     for (int a = 0; a < 3; ++a) {
