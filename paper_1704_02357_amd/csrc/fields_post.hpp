@@ -2,6 +2,8 @@
 // with Y_lm(khat), the product with C and the k binning.  Included by one source per precision.
 #pragma once
 
+#include <type_traits>
+
 #include "fft_common.hpp"
 
 namespace pkm {
@@ -129,12 +131,21 @@ __global__ void __launch_bounds__((PostShape<T, N>::THREADS), (PostShape<T, N>::
             const cx<T>* __restrict__ tw, Frame frm, const unsigned* __restrict__ tiles, int ntiles) {
   using S = PostShape<T, N>;
   constexpr int E = S::E, PT = S::PT, nh = N / 2;
-  const int TP = ALL ? S::TP : (int)blockDim.x / PT;
+  // (constants of the front end where ALL: the offset left to the optimiser costs the 12-point kernels 4 scalar
+  // registers more to spill, 576^3 FP32 post-pass 5.59 -> 5.83 ms)
+  const auto TP = [] {
+    if constexpr (ALL) return std::integral_constant<int, S::TP>{};
+    else return (int)blockDim.x / PT;
+  }();
+  const auto line_lds = [] {
+    if constexpr (ALL) return std::integral_constant<size_t, S::smem(S::TP)>{};
+    else return S::smem((int)blockDim.x / PT);
+  }();
   extern __shared__ __align__(16) unsigned char smem[];
   cx<T>* exch = reinterpret_cast<cx<T>*>(smem);
   cx<T>* cst = exch + TP * S::PITCH;
   cx<T>* twst = cst + TP * S::CPITCH;
-  double* hist = reinterpret_cast<double*>(smem + S::smem(TP));
+  double* hist = reinterpret_cast<double*>(smem + line_lds);
   const int l0rows = with_l0 ? 3 : 0;
   const int nvals = (l0rows + nslots) * nb;
   int* thr_l = reinterpret_cast<int*>(hist + (size_t)copies * nvals);
@@ -205,26 +216,11 @@ __global__ void __launch_bounds__((PostShape<T, N>::THREADS), (PostShape<T, N>::
     const T a0 = (T)(frm.r[0] * fx + frm.r[2] * kz), a1 = (T)(frm.r[3] * fx + frm.r[5] * kz),
             a2 = (T)(frm.r[6] * fx + frm.r[8] * kz);
     const T tf = (T)t;
-    auto form = [&](int e, T& vx, T& vy, T& vz) {
-      const T fy = (S::TIGHT && !CART ? fresh(tf) : tf) + (T)(PT * e - (e >= E / 2 ? N : 0));
+    auto dir = [&](int e, T& vx, T& vy, T& vz) {
+      const T fy = (S::TIGHT ? fresh(tf) : tf) + (T)(PT * e - (e >= E / 2 ? N : 0));
       vx = (a0 + frm.at<T>(1) * fy) * ki[e];
       vy = (a1 + frm.at<T>(4) * fy) * ki[e];
       vz = (a2 + frm.at<T>(7) * fy) * ki[e];
-    };
-    // (the monomials take every component several times, and have no recurrence state: theirs are kept)
-    T ud[CART ? E : 1][3];
-    if constexpr (CART) {
-#pragma unroll
-      for (int e = 0; e < E; ++e) form(e, ud[e][0], ud[e][1], ud[e][2]);
-    }
-    auto dir = [&](int e, T& vx, T& vy, T& vz) {
-      if constexpr (CART) {
-        vx = ud[e][0];
-        vy = ud[e][1];
-        vz = ud[e][2];
-      } else {
-        form(e, vx, vy, vz);
-      }
     };
     __syncthreads();  // C staged
     const unsigned tl_next = tiles[walk.tile(j + walk.step < walk.end ? j + walk.step : j)];
