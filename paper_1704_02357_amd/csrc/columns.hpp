@@ -9,9 +9,9 @@ namespace pkm {
 namespace {
 
 // Elements per thread, columns and threads of the compile-time column passes: N / E rows by 16 columns
-// (128-byte rows in FP32, 256 in FP64), 8 where that exceeds 1024 threads or the LDS of a CU.  Rows of 64 bytes
-// fetch their 128-byte lines twice: 1024^3 combine 7.35 -> 6.32 ms
-// (5.87 since its rows have uniform bases).
+// (128-byte rows in FP32, 256 in FP64), 8 where that exceeds 1024 threads in FP32 or 512 in FP64 (twice the
+// registers: 432, 576, 648 and 768 then have 128-byte rows), or the LDS of a CU.  Rows of 64 bytes fetch their
+// 128-byte lines twice: 1024^3 combine 7.35 -> 6.32 ms (5.87 since its rows have uniform bases).
 __host__ __device__ constexpr int col_e(int n) { return is_pow2(n) ? (n >= 256 ? 16 : 8) : 12; }
 template <typename T> __host__ __device__ constexpr int col_tile(int n) {
   return (n / col_e(n)) * 16 > (sizeof(T) == 4 ? 1024 : 512) || sizeof(cx<T>) * ((size_t)n * 17 + n) > 160 * 1024 ? 8 : 16;
@@ -71,7 +71,8 @@ __global__ void __launch_bounds__((NC > 0 ? (NC / E) * TC : XMAX_THREADS)) k_col
 // not written: 21% of the bytes with edges up to the Nyquist wavenumber.
 // Bound by memory: 512^3, 14 fields: 2.69 ms, 5.3 TB/s (2.75 ms before for every mode; 2.79 with 64-bit addresses
 // per row, of which 14 registers a thread spilled: 30% more written);
-// 432^3, 15 fields 2.85 -> 1.89 ms; 128^3, 289 fields 460 -> 411..455 us.
+// 432^3, 44 fields in groups of 16: 2.85 -> 1.89 ms a group; 128^3, 152 fields 454 -> 411..455 us (5.1
+// TB/s or more).
 // ------------------------------------------------------------------------------------------
 template <typename T, int N>
 __global__ void __launch_bounds__((col_threads<T>(N)), (sizeof(T) == 4 ? 4 : 2))
@@ -202,16 +203,6 @@ __global__ void __launch_bounds__((NC > 0 ? (NC / E) * TC : XMAX_THREADS), (size
 template <typename T> inline size_t colsmem(int n, int tile) {
   return sizeof(cx<T>) * ((size_t)n * (tile + 1) + n);
 }
-
-#define PKM_DISPATCH_E(EVAL, CALL)                  \
-  switch (EVAL) {                                   \
-    case 4: { constexpr int E = 4; CALL; break; }   \
-    case 6: { constexpr int E = 6; CALL; break; }   \
-    case 8: { constexpr int E = 8; CALL; break; }   \
-    case 12: { constexpr int E = 12; CALL; break; } \
-    case 16: { constexpr int E = 16; CALL; break; } \
-    default: return hipErrorInvalidValue;           \
-  }
 
 // Compile-time column kernels for shapes other than the built-in one (a caller's or a tuned shape).
 #define PKM_TRY_COL_SHAPES(TRY) TRY(64, 8, 8) TRY(128, 8, 8) TRY(256, 8, 8) TRY(512, 8, 8) TRY(1024, 8, 4)

@@ -103,18 +103,6 @@ __device__ __forceinline__ void xf_regs(cx<T>* lds, int off, int es, const LineR
     for (int e = 0; e < E; ++e) u[e] = lds[off + padi<PAD>(t + rt.pt * e) * es];
   }
 }
-// Same with the input line already in LDS (filled, and a block barrier since).
-template <typename T, int E, bool INV, int PAD, int LC, bool WAVE>
-__device__ __forceinline__ void xf_lds_in(cx<T>* lds, int off, int es, const LineRt& rt, int t, cx<T>* u,
-                                          const cx<T>* twst, const cx<T>* __restrict__ twl) {
-  if constexpr (LC > 0) {
-    ct_fft_lds_in<T, E, INV, PAD, LC, WAVE>(lds, off, es, t, u, twst);
-  } else {
-    lds_fft<T, E, INV, PAD>(lds, off, es, rt.L, rt.sched, rt.nst, t, rt.pt, twl, rt.ntw);
-#pragma unroll
-    for (int e = 0; e < E; ++e) u[e] = lds[off + padi<PAD>(t + rt.pt * e) * es];
-  }
-}
 // LDS entries of the per-stage twiddle table (compile-time path only).
 template <int E, int LC> __host__ __device__ constexpr int twst_size() { return LC > 0 ? ct_tw_total(E, LC) : 0; }
 
@@ -168,6 +156,17 @@ __device__ __forceinline__ void hist_flush(const double* h, int copies, int nval
   X(16) X(24) X(32) X(36) X(48) X(64) X(72) X(96) X(108) X(128) X(144) X(192) X(216) X(256) X(288)    \
   X(324) X(384) X(432) X(512) X(576) X(648) X(768) X(864) X(972) X(1024)
 #endif
+
+// CALL with E the run-time number of elements per thread.
+#define PKM_DISPATCH_E(EVAL, CALL)                  \
+  switch (EVAL) {                                   \
+    case 4: { constexpr int E = 4; CALL; break; }   \
+    case 6: { constexpr int E = 6; CALL; break; }   \
+    case 8: { constexpr int E = 8; CALL; break; }   \
+    case 12: { constexpr int E = 12; CALL; break; } \
+    case 16: { constexpr int E = 16; CALL; break; } \
+    default: return hipErrorInvalidValue;           \
+  }
 
 constexpr bool is_pow2(int n) { return (n & (n - 1)) == 0; }
 // Radix stages of the compile-time transform.

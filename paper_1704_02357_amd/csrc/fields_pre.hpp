@@ -46,8 +46,10 @@ template <typename T, int N> struct PreShape {
 // Finished lines are parked in LDS and stored transposed, G consecutive y per piece.  Planes at and
 // beyond the last k edge (kz_live) are not written.
 // 512^3, 14 fields of l <= 4: 2.93 -> 2.55 ms (bound by the stores and by the harmonics and butterflies between
-// them; stores of 64 bytes a piece took 2.8 ms); 384^3 FP64 3.81 -> 2.98 ms; 432^3, 15 fields: 5.22 -> 2.40 ms
-// (a kernel of run-time lengths before); 256^3 345 -> 278 us; 128^3, 289 fields of l <= 16: 355 -> 398 us.
+// them; stores of 64 bytes a piece took 2.8 ms); 384^3 FP64 3.81 -> 2.98 ms; 432^3, 44 fields in groups of 16:
+// 5.22 -> 2.40 ms a group (a kernel of run-time lengths before); 256^3 345 -> 278 us.  128^3, 152 fields of
+// l <= 16: 329 -> 368 us, 3.5 TB/s written and vector units 45% busy: all blocks are resident at once and each takes
+// its 80 entries one after the other, a barrier an entry.
 // ------------------------------------------------------------------------------------------
 template <typename T, int N>
 __global__ void __launch_bounds__((PreShape<T, N>::THREADS), (PreShape<T, N>::MINW))

@@ -17,10 +17,7 @@ struct FftShape {
   int nst_z;
   int tile;         // columns per column-pass tile
   int zlines;       // lines per z-pass block
-  int e_post;       // elements per thread in the post-pass (last transform + binning)
-  uint32_t sched_post;
-  int nst_post;
-  int tile_post;    // columns per post-pass tile
+  int e_post, tile_post;  // checked, and in the limit on k bins; the post-pass has its own shape per side
   int cus;          // compute units of the device (0: unknown)
   bool col_builtin;  // e_col and tile are the built-in choice: the column passes run the
                      // kernels compiled for the side

@@ -269,23 +269,14 @@ static size_t zsmem(const FftShape& fs, size_t cs) {
   return cs * ((size_t)fs.zlines * zpitch(fs.n / 2) + fs.n + fs.n / 2);
 }
 size_t zpass_smem_bytes(const FftShape& fs, bool fp64) {
-  // shapes are held to the LDS of two line regions per block
+  // (two line regions a block, as when the pre-pass shared the shape: the limit that callers' shapes are held to;
+  // the z passes take one)
   const size_t cs = fp64 ? sizeof(double2) : sizeof(float2);
   return cs * (2 * (size_t)fs.zlines * zpitch(fs.n / 2) + fs.n + fs.n / 2);
 }
 size_t colpass_smem_bytes(const FftShape& fs, bool fp64) {
   return (fp64 ? sizeof(double2) : sizeof(float2)) * ((size_t)fs.n * (fs.tile + 1) + fs.n);
 }
-
-#define PKM_DISPATCH_E(EVAL, CALL)                  \
-  switch (EVAL) {                                   \
-    case 4: { constexpr int E = 4; CALL; break; }   \
-    case 6: { constexpr int E = 6; CALL; break; }   \
-    case 8: { constexpr int E = 8; CALL; break; }   \
-    case 12: { constexpr int E = 12; CALL; break; } \
-    case 16: { constexpr int E = 16; CALL; break; } \
-    default: return hipErrorInvalidValue;           \
-  }
 
 // Compile-time instantiations: (N, E, TC) triples matching the plan's shape rules for FP32
 // and FP64 at the power-of-two sizes and at 384 and 768; anything else runs the generic

@@ -1133,12 +1133,11 @@ bool make_shape(const pkm_params& p, FftShape* out) {
   // 256..1024 take 16 (the autotuner's pick at 512^3)
   const bool pow2_table = n >= 256 && n <= 1024 && (n & (n - 1)) == 0;
   if (fp64 && fs.e_col == 16 && !pow2_table) fs.e_col = 8;
-  // z lines: 2E nodes per thread carry the harmonic recurrence in the pre-pass, which spills
-  // at 12 (radix-3 lengths) as it would at 16
+  // z lines: at most 8 elements (6 for radix-3 lengths), and 4 in FP64 at 512.  These date from a pre-pass
+  // that shared the shape and its registers; the z passes alone, which use it now, are 8% slower with 4 than
+  // with 8 there.
   if (fs.e_z == 16) fs.e_z = 8;
   if (fs.e_z == 12) fs.e_z = 6;
-  // FP64 at 512: 4 elements per thread keep the pre-pass at 228 VGPRs and two waves per SIMD
-  // (8 need 256 VGPRs and 149 AGPRs: one wave); measured 7% faster, the z pass 8% slower
   if (fp64 && n == 512) fs.e_z = 4;
   if (!fs.e_col || !fs.e_z || !make_sched(n, fs.e_col, &fs.sched_col, &fs.nst_col) ||
       !make_sched(n / 2, fs.e_z, &fs.sched_z, &fs.nst_z)) {
@@ -1150,32 +1149,23 @@ bool make_shape(const pkm_params& p, FftShape* out) {
   const int pt_col = n / fs.e_col;
   while (fs.tile > 1 && (pt_col * fs.tile > 512 || (n / 2) % fs.tile || colpass_smem_bytes(fs, fp64) > 160 * 1024))
     fs.tile /= 2;
-  // post-pass: at most 8 elements per thread (register budget of the fused recurrence), 6 for
-  // lengths with a factor 3, except FP64 at 384 and 768: there 12 (one wave per line and two
-  // fewer radix stages) measured 22% (384) and 39% (768) faster than 6, where in FP32 the
-  // two took the same time
+  // e_post and tile_post select no kernel (the post-pass has its own shape per side); they make the default
+  // limit on k bins, which stays where it was
   fs.e_post = fs.e_col > 8 && fs.e_col % 8 == 0 ? 8 : fs.e_col;
   if (fs.e_post == 12 && !(fp64 && (n == 384 || n == 768))) fs.e_post = 6;
-  if (!make_sched(n, fs.e_post, &fs.sched_post, &fs.nst_post)) {
-    return false;
-  }
-  // 256-thread post-pass blocks (several resident per CU); narrow tiles share 128-byte rows
-  // through L2 because consecutive tiles run on the same XCD
+  uint32_t sched;
+  int stages;
+  if (!make_sched(n, fs.e_post, &sched, &stages)) return false;
   {
     const int pt_post = n / fs.e_post;
     int tp = std::max(1, 256 / pt_post);
     tp = std::min(tp, 16);
     while (tp > 1 && (n / 2) % tp) tp /= 2;
-    // a line wider than a wavefront synchronises its whole block at every radix stage: one
-    // line per block (with more blocks per CU) measured 8-16% faster at 768 and 1024
     if (pt_post > 64) tp = 1;
     fs.tile_post = tp;
   }
-  // z lines per block: a power of two dividing n (a block's lines share one x plane, and the
-  // pre-pass writes them as runs of consecutive y into the kz-major field buffers)
+  // z lines per block: a power of two dividing n, at most 256 threads per block, or 512 for FP32 from N = 512 up
   const int pt_z = (n / 2) / fs.e_z;
-  // At most 256 threads per block, or 512 for FP32 from N = 512 up (16 lines of 512: the
-  // pre-pass then writes 128-byte runs, measured faster than the 64-byte runs of 8 lines).
   const int zmax = (fp64 || n < 512) ? 256 : 512;
   fs.zlines = 1;
   for (;;) {
@@ -1214,7 +1204,9 @@ bool apply_shape(const pkm_params& p, const pkm_shape& sh, FftShape* fs, int* ts
       zpass_smem_bytes(f, fp64) > 160 * 1024)
     return fail("z-pass lines break a kernel limit");
   if (sh.e_post) {
-    if (!is_elem(sh.e_post) || !make_sched(n, sh.e_post, &f.sched_post, &f.nst_post)) return fail("bad e_post");
+    uint32_t sched;
+    int stages;
+    if (!is_elem(sh.e_post) || !make_sched(n, sh.e_post, &sched, &stages)) return fail("bad e_post");
     f.e_post = sh.e_post;
   }
   if (sh.tile_post) f.tile_post = sh.tile_post;
