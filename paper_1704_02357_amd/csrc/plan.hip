@@ -1451,7 +1451,7 @@ int64_t footprint(const pkm_params* p, int ell_max, int n_edges, int64_t n_parti
   const int64_t ts = 8;
   const int64_t ntiles = (n / ts) * (n / ts) * (n / ts);
   const int64_t det = p->deterministic ? 8 * n * n * n * (p->interlaced ? 2 : 1) : 0;
-  return meshes * mesh + pads + 80 * n_particles + partial + 8 * ntiles + det + (4 << 20);
+  return meshes * mesh + pads + 80 * n_particles + partial + 8 * ntiles + 4 * (int64_t)tiles + det + (4 << 20);
 }
 
 }  // namespace pkm_internal
