@@ -502,6 +502,19 @@ __device__ __forceinline__ void ct_later_stages(cx<T>* lds, int off, int t, cx<T
     for (int s = 0; s < RL; ++s) u[q + s * NBL] = v[q * RL + s];
 }
 
+// Same as ct_fft_regs with the input line already in LDS (filled and made visible by the caller).
+template <typename T, int E, bool INV, int PAD, int L, bool WAVE>
+__device__ __forceinline__ void ct_fft_lds_in(cx<T>* lds, int off, int es, int t, cx<T>* u, const cx<T>* twst) {
+  constexpr int RL = ct_last_radix(E, L), NBL = E / RL;
+  cx<T> v[E];
+  ct_gather<T, E, PAD, L, 1>(lds, off, es, t, v);
+  ct_rest<T, E, INV, PAD, L, WAVE, 1>(lds, off, es, t, v, twst);
+#pragma unroll
+  for (int q = 0; q < NBL; ++q)
+#pragma unroll
+    for (int s = 0; s < RL; ++s) u[q + s * NBL] = v[q * RL + s];
+}
+
 // Radix schedule packed 4 bits per stage (stage 0 in the low bits), nst stages.
 template <typename T, int E, bool INV, int PAD = 0>
 __device__ __forceinline__ void lds_fft(cx<T>* lds, int off, int es, int L, uint32_t sched, int nst, int t, int Pt,
