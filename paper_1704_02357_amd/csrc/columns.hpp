@@ -55,7 +55,7 @@ __global__ void __launch_bounds__((NC > 0 ? (NC / E) * TC : XMAX_THREADS)) k_col
   cx<T>* twst = twl;
   if constexpr (NC > 0) ct_twiddles<T, E, NC, NC>(twst, tw); else stage_twiddles<T>(twl, tw, n);
   const LineRt rt{n, sched, nst, pt, n};
-  xf_regs<T, E, INV, 0, NC, false>(lds, c, pitch, rt, t, u, twst, twl);
+  xf_regs<T, E, INV, 0, NC, false, true>(lds, c, pitch, rt, t, u, twst, twl);
   if (!live) return;
 #pragma unroll
   for (int e = 0; e < E; ++e) gstore32<T>(buf + pt * e * row_stride, off, u[e]);
@@ -168,9 +168,9 @@ __global__ void __launch_bounds__((NC > 0 ? (NC / E) * TC : XMAX_THREADS), (size
   cx<T>* twst = twl;
   if constexpr (NC > 0) ct_twiddles<T, E, NC, NC>(twst, tw); else stage_twiddles<T>(twl, tw, n);
   const LineRt rt{n, sched, nst, pt, n};
-  xf_regs<T, E, false, 0, NC, false>(lds, c, pitch, rt, t, a1, twst, twl);
+  xf_regs<T, E, false, 0, NC, false, true>(lds, c, pitch, rt, t, a1, twst, twl);
   if (interlaced) {
-    xf_regs<T, E, false, 0, NC, false>(lds, c, pitch, rt, t, a2, twst, twl);
+    xf_regs<T, E, false, 0, NC, false, true>(lds, c, pitch, rt, t, a2, twst, twl);
     const cx<T> pyz = cmul<T>(phase[y], phase[kz]);
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -190,7 +190,7 @@ __global__ void __launch_bounds__((NC > 0 ? (NC / E) * TC : XMAX_THREADS), (size
     if (live) gstore32<T>(cout + base + pt * e * rs, off, v);
   }
   if (gout == nullptr) return;
-  xf_regs<T, E, true, 0, NC, false>(lds, c, pitch, rt, t, a1, twst, twl);
+  xf_regs<T, E, true, 0, NC, false, true>(lds, c, pitch, rt, t, a1, twst, twl);
   if (!live) return;
 #pragma unroll
   for (int e = 0; e < E; ++e) gstore32<T>(gout + base + pt * e * rs, off, a1[e]);

@@ -45,20 +45,32 @@ template <typename T, bool INV> __device__ __forceinline__ void dft4(cx<T>* v) {
   v[3] = csub<T>(b0, b1);
 }
 
-template <typename T, bool INV> __device__ __forceinline__ void dft3(cx<T>* v) {
+// a times a constant.  Rounded to 24 bits, sqrt(1/2), sqrt(3)/2 and cos(pi/8) are 1.7e-8, 1.8e-8 and 3.1e-8 too
+// small, always the same way, and the power of a line shrinks by what the constants of its butterflies lack
+// (4.1e-8 at 128 points, 5.0e-8 at 144, twiddles included), which no average over modes removes.  FINE carries the
+// constant's remainder inside the one rounding: 2.4e-8 and 0.8e-8.  The transforms of the painted meshes take it,
+// whose error goes into P_0; the passes over the weighted fields, bound by vector instructions, lose 2 to 3% with it
+// where radices 3, 6 and 12 run.  FP32 against FP64, 128^3 survey, 60 seeds: P_l 1.84e-7 -> 1.39e-7; 432^3, l <= 8:
+// 2.9e-7 -> 1.6e-7; times unchanged.
+template <typename T, bool FINE> __device__ __forceinline__ T times_c(T a, double c) {
+  if (FINE && sizeof(T) == 4 && (double)(T)c != c) return (T)__builtin_fmaf(a, (T)c, a * (T)(c - (double)(T)c));
+  return a * (T)c;
+}
+
+template <typename T, bool INV, bool FINE> __device__ __forceinline__ void dft3(cx<T>* v) {
   const T h = T(0.5);
-  const T s3 = INV ? T(-0.86602540378443864676) : T(0.86602540378443864676);
+  const double s3 = INV ? -0.86602540378443864676 : 0.86602540378443864676;
   cx<T> t1 = cadd<T>(v[1], v[2]);
   cx<T> t2 = csub<T>(v[1], v[2]);
   cx<T> m = mk<T>(v[0].x - h * t1.x, v[0].y - h * t1.y);
   // forward: y1 = m - i s3 t2, y2 = m + i s3 t2
-  cx<T> it = mk<T>(s3 * t2.y, -s3 * t2.x);  // -i * s3 * t2
+  cx<T> it = mk<T>(times_c<T, FINE>(t2.y, s3), times_c<T, FINE>(t2.x, -s3));  // -i * s3 * t2
   v[0] = cadd<T>(v[0], t1);
   v[1] = cadd<T>(m, it);
   v[2] = csub<T>(m, it);
 }
 
-template <typename T, bool INV> __device__ __forceinline__ void dft6(cx<T>* v) {
+template <typename T, bool INV, bool FINE> __device__ __forceinline__ void dft6(cx<T>* v) {
   // split t -> (t, t+3): a_t = x_t + x_{t+3}, b_t = (x_t - x_{t+3}) W6^t
   cx<T> a[3], b[3];
 #pragma unroll
@@ -66,55 +78,56 @@ template <typename T, bool INV> __device__ __forceinline__ void dft6(cx<T>* v) {
     a[t] = cadd<T>(v[t], v[t + 3]);
     b[t] = csub<T>(v[t], v[t + 3]);
   }
-  const T c1 = T(0.5), s1 = INV ? T(0.86602540378443864676) : T(-0.86602540378443864676);
-  b[1] = cmul<T>(b[1], mk<T>(c1, s1));    // W6^1
-  b[2] = cmul<T>(b[2], mk<T>(-c1, s1));   // W6^2
-  dft3<T, INV>(a);
-  dft3<T, INV>(b);
+  const double s1 = INV ? 0.86602540378443864676 : -0.86602540378443864676;
+  auto rot = [&](cx<T> a, T c) { return mk<T>(a.x * c - times_c<T, FINE>(a.y, s1), times_c<T, FINE>(a.x, s1) + a.y * c); };
+  b[1] = rot(b[1], T(0.5));    // W6^1
+  b[2] = rot(b[2], T(-0.5));   // W6^2
+  dft3<T, INV, FINE>(a);
+  dft3<T, INV, FINE>(b);
   v[0] = a[0]; v[2] = a[1]; v[4] = a[2];
   v[1] = b[0]; v[3] = b[1]; v[5] = b[2];
 }
 
-template <typename T, bool INV> __device__ __forceinline__ void dft8(cx<T>* v) {
+template <typename T, bool INV, bool FINE> __device__ __forceinline__ void dft8(cx<T>* v) {
   cx<T> a[4], b[4];
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     a[t] = cadd<T>(v[t], v[t + 4]);
     b[t] = csub<T>(v[t], v[t + 4]);
   }
-  const T r = T(0.70710678118654752440);
+  const double r = 0.70710678118654752440;
   // b_t *= W8^t
-  b[1] = INV ? mk<T>(r * (b[1].x - b[1].y), r * (b[1].x + b[1].y))
-             : mk<T>(r * (b[1].x + b[1].y), r * (b[1].y - b[1].x));
+  const T p1 = times_c<T, FINE>(b[1].x + b[1].y, r), m1 = times_c<T, FINE>(b[1].x - b[1].y, r);
+  const T p3 = times_c<T, FINE>(b[3].x + b[3].y, r), m3 = times_c<T, FINE>(b[3].x - b[3].y, r);
+  b[1] = INV ? mk<T>(m1, p1) : mk<T>(p1, -m1);
   b[2] = rot_mi<T, INV>(b[2]);
-  b[3] = INV ? mk<T>(-r * (b[3].x + b[3].y), r * (b[3].x - b[3].y))
-             : mk<T>(r * (b[3].y - b[3].x), -r * (b[3].x + b[3].y));
+  b[3] = INV ? mk<T>(-p3, m3) : mk<T>(-m3, -p3);
   dft4<T, INV>(a);
   dft4<T, INV>(b);
   v[0] = a[0]; v[2] = a[1]; v[4] = a[2]; v[6] = a[3];
   v[1] = b[0]; v[3] = b[1]; v[5] = b[2]; v[7] = b[3];
 }
 
-// a * exp(-+2 pi i j / D) for the constant (cos, sin) of that angle.
-template <typename T, bool INV> __device__ __forceinline__ cx<T> rot_c(cx<T> a, double c, double s) {
-  const T cc = (T)c, ss = INV ? (T)s : (T)(-s);
-  return mk<T>(a.x * cc - a.y * ss, a.x * ss + a.y * cc);
+// a * exp(-+2 pi i j / 12) for the constant (cos, sin) of that angle, one of them +-1/2.
+template <typename T, bool INV, bool FINE> __device__ __forceinline__ cx<T> rot_c(cx<T> a, double c, double s) {
+  const double ss = INV ? s : -s;
+  return mk<T>(times_c<T, FINE>(a.x, c) - times_c<T, FINE>(a.y, ss), times_c<T, FINE>(a.x, ss) + times_c<T, FINE>(a.y, c));
 }
 
 // 12 = 4 x 3: t = t0 + 4 t1, s = s1 + 3 s0; DFTs of 3 over t1, twiddles W12^(t0 s1), DFTs of 4.
-template <typename T, bool INV> __device__ __forceinline__ void dft12(cx<T>* v) {
+template <typename T, bool INV, bool FINE> __device__ __forceinline__ void dft12(cx<T>* v) {
   const double h = 0.86602540378443864676;
   cx<T> a[4][3];
 #pragma unroll
   for (int t0 = 0; t0 < 4; ++t0) {
 #pragma unroll
     for (int t1 = 0; t1 < 3; ++t1) a[t0][t1] = v[t0 + 4 * t1];
-    dft3<T, INV>(a[t0]);
+    dft3<T, INV, FINE>(a[t0]);
   }
-  a[1][1] = rot_c<T, INV>(a[1][1], h, 0.5);      // W12^1
-  a[1][2] = rot_c<T, INV>(a[1][2], 0.5, h);      // W12^2
-  a[2][1] = rot_c<T, INV>(a[2][1], 0.5, h);      // W12^2
-  a[2][2] = rot_c<T, INV>(a[2][2], -0.5, h);     // W12^4
+  a[1][1] = rot_c<T, INV, FINE>(a[1][1], h, 0.5);      // W12^1
+  a[1][2] = rot_c<T, INV, FINE>(a[1][2], 0.5, h);      // W12^2
+  a[2][1] = rot_c<T, INV, FINE>(a[2][1], 0.5, h);      // W12^2
+  a[2][2] = rot_c<T, INV, FINE>(a[2][2], -0.5, h);     // W12^4
   a[3][1] = rot_mi<T, INV>(a[3][1]);             // W12^3
   a[3][2] = mk<T>(-a[3][2].x, -a[3][2].y);       // W12^6
 #pragma unroll
@@ -128,20 +141,14 @@ template <typename T, bool INV> __device__ __forceinline__ void dft12(cx<T>* v) 
   }
 }
 
-// The rotations of a DFT of 16.  In FP32 cos(pi/8) rounded is 3.1e-8 too small and sqrt(1/2) 1.7e-8, always the
-// same way, and the power of a line shrinks by what its constants lack: the two such DFTs of a length of 256 took
-// 5.3e-8 of it, radices 8, 8 and 4 take 4.1e-8.  A product here is rounded once with the constant's remainder
-// inside (that of sin(pi/8), 1.6e-8 of it, is left): 1.0e-8 at 256 points, 3.1e-8 at 1024 (5.3e-8 before, 5.0e-8
-// with radices 8, 8, 8 and 2).
-template <typename T> __device__ __forceinline__ T times_c(T a, double c) {
-  if constexpr (sizeof(T) == 4) return __builtin_fmaf(a, (T)c, a * (T)(c - (double)(T)c));
-  else return a * c;
-}
+// The rotations of a DFT of 16, always FINE: the two such DFTs of a length of 256 took 5.3e-8 of a line's power with
+// rounded constants, where radices 8, 8 and 4 take 4.1e-8; 1.0e-8 now (the remainder of sin(pi/8) is left out).  1024
+// points: 5.3e-8, 5.0e-8 with radices 8, 8, 8 and 2, 1.4e-8 now.
 // a * exp(-+2 pi i j / 16): j = 1 and 9 (FIRST: the larger constant on the diagonal; the sign of both with 9) or 3.
 template <typename T, bool INV, bool FIRST> __device__ __forceinline__ cx<T> rot_16(cx<T> a, double sign) {
   const double c1 = 0.92387953251128675613, c3 = 0.38268343236508977173;
   const T s3 = (T)(sign * c3);
-  const T px = times_c<T>(a.x, sign * c1), py = times_c<T>(a.y, sign * c1);
+  const T px = times_c<T, true>(a.x, sign * c1), py = times_c<T, true>(a.y, sign * c1);
   // forward: (x + i y)(c - i s)
   if constexpr (FIRST) return INV ? mk<T>(px - a.y * s3, a.x * s3 + py) : mk<T>(px + a.y * s3, py - a.x * s3);
   else return INV ? mk<T>(a.x * s3 - py, px + a.y * s3) : mk<T>(a.x * s3 + py, a.y * s3 - px);
@@ -149,7 +156,7 @@ template <typename T, bool INV, bool FIRST> __device__ __forceinline__ cx<T> rot
 // j = 2, and 6 (the same times -+i)
 template <typename T, bool INV> __device__ __forceinline__ cx<T> rot_8(cx<T> a) {
   const double r = 0.70710678118654752440;
-  const T p = times_c<T>(a.x + a.y, r), m = times_c<T>(a.x - a.y, r);
+  const T p = times_c<T, true>(a.x + a.y, r), m = times_c<T, true>(a.x - a.y, r);
   return INV ? mk<T>(m, p) : mk<T>(p, -m);
 }
 
@@ -182,13 +189,13 @@ template <typename T, bool INV> __device__ __forceinline__ void dft16(cx<T>* v) 
   }
 }
 
-template <typename T, int R, bool INV> __device__ __forceinline__ void dft_r(cx<T>* v) {
+template <typename T, int R, bool INV, bool FINE = false> __device__ __forceinline__ void dft_r(cx<T>* v) {
   if constexpr (R == 2) dft2<T, INV>(v);
-  else if constexpr (R == 3) dft3<T, INV>(v);
+  else if constexpr (R == 3) dft3<T, INV, FINE>(v);
   else if constexpr (R == 4) dft4<T, INV>(v);
-  else if constexpr (R == 6) dft6<T, INV>(v);
-  else if constexpr (R == 8) dft8<T, INV>(v);
-  else if constexpr (R == 12) dft12<T, INV>(v);
+  else if constexpr (R == 6) dft6<T, INV, FINE>(v);
+  else if constexpr (R == 8) dft8<T, INV, FINE>(v);
+  else if constexpr (R == 12) dft12<T, INV, FINE>(v);
   else dft16<T, INV>(v);
 }
 
@@ -236,7 +243,7 @@ __device__ __forceinline__ void stockham_stage(cx<T>* lds, int off, int es, int 
         v[q * R + s] = cmul<T>(v[q * R + s], w);
       }
     }
-    dft_r<T, R, INV>(&v[q * R]);
+    dft_r<T, R, INV, true>(&v[q * R]);  // (only transforms of the painted meshes come here)
 #pragma unroll
     for (int s = 0; s < R; ++s) lds[off + padi<PAD>(base + s * m) * es] = v[q * R + s];
   }
@@ -406,7 +413,7 @@ __device__ __forceinline__ void ct_gather(const cx<T>* lds, int off, int es, int
       else v[q * R + s] = lds[off + pad(t + q * PT + s * LR) * es];
     }
 }
-template <typename T, int E, bool INV, int L, int M>
+template <typename T, int E, bool INV, int L, int M, bool FINE = false>
 __device__ __forceinline__ void ct_butterflies(int t, cx<T>* v, const cx<T>* twst) {
   constexpr int R = ct_radix(E, L / M), PT = L / E, NB = E / R, OFF = ct_tw_off(E, L, M);
 #pragma unroll
@@ -420,7 +427,7 @@ __device__ __forceinline__ void ct_butterflies(int t, cx<T>* v, const cx<T>* tws
         v[q * R + s] = cmul<T>(v[q * R + s], w);
       }
     }
-    dft_r<T, R, INV>(&v[q * R]);
+    dft_r<T, R, INV, FINE>(&v[q * R]);
   }
 }
 // Outputs y_s of butterfly b go to (b/M) M R + (b mod M) + s M.
@@ -441,23 +448,23 @@ __device__ __forceinline__ void ct_scatter(cx<T>* lds, int off, int es, int t, c
     }
   }
 }
-template <typename T, int E, bool INV, int PAD, int L, bool WAVE, int M>
+template <typename T, int E, bool INV, int PAD, int L, bool WAVE, int M, bool FINE = false>
 __device__ __forceinline__ void ct_rest(cx<T>* lds, int off, int es, int t, cx<T>* v, const cx<T>* twst) {
-  ct_butterflies<T, E, INV, L, M>(t, v, twst);
+  ct_butterflies<T, E, INV, L, M, FINE>(t, v, twst);
   constexpr int R = ct_radix(E, L / M);
   if constexpr (M * R < L) {
     ct_sync<WAVE>();
     ct_scatter<T, E, PAD, L, M>(lds, off, es, t, v);
     ct_sync<WAVE>();
     ct_gather<T, E, PAD, L, M * R>(lds, off, es, t, v);
-    ct_rest<T, E, INV, PAD, L, WAVE, M * R>(lds, off, es, t, v, twst);
+    ct_rest<T, E, INV, PAD, L, WAVE, M * R, FINE>(lds, off, es, t, v, twst);
   }
 }
 
 // Transform of u in place (registers).  The caller must have finished every read of the
 // line's LDS slots by the threads of the line (ct_sync<WAVE> or stronger) and the twiddle
 // table must be visible.  On return the LDS slots hold intermediate data.
-template <typename T, int E, bool INV, int PAD, int L, bool WAVE>
+template <typename T, int E, bool INV, int PAD, int L, bool WAVE, bool FINE = false>
 __device__ __forceinline__ void ct_fft_regs(cx<T>* lds, int off, int es, int t, cx<T>* u, const cx<T>* twst) {
   constexpr int R0 = ct_radix(E, L), NB0 = E / R0;
   constexpr int RL = ct_last_radix(E, L), NBL = E / RL;
@@ -466,7 +473,7 @@ __device__ __forceinline__ void ct_fft_regs(cx<T>* lds, int off, int es, int t, 
   for (int q = 0; q < NB0; ++q)
 #pragma unroll
     for (int s = 0; s < R0; ++s) v[q * R0 + s] = u[q + s * NB0];
-  ct_rest<T, E, INV, PAD, L, WAVE, 1>(lds, off, es, t, v, twst);
+  ct_rest<T, E, INV, PAD, L, WAVE, 1, FINE>(lds, off, es, t, v, twst);
 #pragma unroll
   for (int q = 0; q < NBL; ++q)
 #pragma unroll
@@ -503,12 +510,12 @@ __device__ __forceinline__ void ct_later_stages(cx<T>* lds, int off, int t, cx<T
 }
 
 // Same as ct_fft_regs with the input line already in LDS (filled and made visible by the caller).
-template <typename T, int E, bool INV, int PAD, int L, bool WAVE>
+template <typename T, int E, bool INV, int PAD, int L, bool WAVE, bool FINE = false>
 __device__ __forceinline__ void ct_fft_lds_in(cx<T>* lds, int off, int es, int t, cx<T>* u, const cx<T>* twst) {
   constexpr int RL = ct_last_radix(E, L), NBL = E / RL;
   cx<T> v[E];
   ct_gather<T, E, PAD, L, 1>(lds, off, es, t, v);
-  ct_rest<T, E, INV, PAD, L, WAVE, 1>(lds, off, es, t, v, twst);
+  ct_rest<T, E, INV, PAD, L, WAVE, 1, FINE>(lds, off, es, t, v, twst);
 #pragma unroll
   for (int q = 0; q < NBL; ++q)
 #pragma unroll

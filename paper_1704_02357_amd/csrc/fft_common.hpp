@@ -88,11 +88,11 @@ struct LineRt {
 // Line transform with the line in registers on entry and exit (element e = position
 // t + pt*e).  LC > 0: compile-time schedule (WAVE = the line lies inside one wavefront);
 // LC = 0: generic schedule through the LDS line, block-wide barriers.
-template <typename T, int E, bool INV, int PAD, int LC, bool WAVE>
+template <typename T, int E, bool INV, int PAD, int LC, bool WAVE, bool FINE = false>
 __device__ __forceinline__ void xf_regs(cx<T>* lds, int off, int es, const LineRt& rt, int t, cx<T>* u,
                                         const cx<T>* twst, const cx<T>* __restrict__ twl) {
   if constexpr (LC > 0) {
-    ct_fft_regs<T, E, INV, PAD, LC, WAVE>(lds, off, es, t, u, twst);
+    ct_fft_regs<T, E, INV, PAD, LC, WAVE, FINE>(lds, off, es, t, u, twst);
   } else {
     __syncthreads();
 #pragma unroll

@@ -63,7 +63,7 @@ __global__ void __launch_bounds__(zmax_threads<T>()) k_zfwd(int n_rt, int g_rt, 
   cx<T>* line = lds + g * lp;
   if constexpr (NC > 0) {
     cx<T> u[E];
-    ct_fft_lds_in<T, E, false, ZPAD, NC / 2, WAVE>(lds, g * lp, 1, t, u, twst);
+    ct_fft_lds_in<T, E, false, ZPAD, NC / 2, WAVE, true>(lds, g * lp, 1, t, u, twst);
 #pragma unroll
     for (int e = 0; e < E; ++e) line[padi<ZPAD>(t + pt * e)] = u[e];
     ct_sync<WAVE>();
@@ -107,7 +107,7 @@ __global__ void __launch_bounds__(zmax_threads<T>()) k_zinv(int n_rt, int g_rt, 
   cx<T> z[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) z[e] = c2r_split<T>(line, t + pt * e, nh, twl);
-  xf_regs<T, E, true, ZPAD, NC / 2, WAVE>(lds, g * lp, 1, rt, t, z, twst, twl);
+  xf_regs<T, E, true, ZPAD, NC / 2, WAVE, true>(lds, g * lp, 1, rt, t, z, twst, twl);
   cx<T>* dst = reinterpret_cast<cx<T>*>(real_out) + (line0 + g) * nh;
 #pragma unroll
   for (int e = 0; e < E; ++e) gstore<T>(dst, t + pt * e, cscale<T>(z[e], scale));
