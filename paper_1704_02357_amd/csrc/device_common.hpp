@@ -143,7 +143,7 @@ template <typename T, bool INV, bool FINE> __device__ __forceinline__ void dft12
 
 // The rotations of a DFT of 16, always FINE: the two such DFTs of a length of 256 took 5.3e-8 of a line's power with
 // rounded constants, where radices 8, 8 and 4 take 4.1e-8; 1.0e-8 now (the remainder of sin(pi/8) is left out).  1024
-// points: 5.3e-8, 5.0e-8 with radices 8, 8, 8 and 2, 1.4e-8 now.
+// points: 5.3e-8, 5.0e-8 with radices 8, 8, 8 and 2, 3.1e-8 now (1.4e-8 with FINE radix-8 stages).
 // a * exp(-+2 pi i j / 16): j = 1 and 9 (FIRST: the larger constant on the diagonal; the sign of both with 9) or 3.
 template <typename T, bool INV, bool FIRST> __device__ __forceinline__ cx<T> rot_16(cx<T> a, double sign) {
   const double c1 = 0.92387953251128675613, c3 = 0.38268343236508977173;

@@ -118,7 +118,7 @@ template <int CTRL, typename... V> __device__ __forceinline__ void quad_merge(in
 // from the mode numbers (linear in fy) where the recurrence needs them.
 // 512^3, 14 fields of l <= 4: 2.64 ms as packed half lines over every mode, 1.33 now (4.5 TB/s; the rest is
 // the harmonics and the exchanges); 432^3, 44 fields of l <= 8 in groups of 16: 5.85 -> 1.57 ms a group (a kernel of
-// run-time lengths before); 1024^3 19.0 -> 14.5; 384^3 FP64 2.60 -> 1.5; 256^3 337 -> 221 us; 128^3, 152 fields of
+// run-time lengths before); 1024^3 18.9 -> 14.6; 384^3 FP64 2.60 -> 1.5; 256^3 337 -> 221 us; 128^3, 152 fields of
 // l <= 16: 297 -> 248 us; 64^3 FP64, l <= 4: 31 -> 23 us.
 // ALL: blocks of all TP lines.  Else of as many (fewer) as the launch has threads for: requests whose
 // histograms leave no room for TP lines in the LDS of a CU.
