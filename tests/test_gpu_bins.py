@@ -100,3 +100,31 @@ def test_few_modes_equal_direct_sums(gpu, n, top, prec):
     ref = {"poles": poles, "n_modes": counts.astype(np.int64), "k_mean": kmean, "alpha": 0.0,
            "norm_I": got["norm_I"], "shot_noise": got["shot_noise"]}
     assert_pole_parity(dict(got, alpha=0.0), ref, prec, f"side {n} top {top}")
+
+
+def test_many_bins_replayed_as_graph(gpu):
+    """Blocks of fewer lines inside a captured batch: every replay, with eager work between, equals the
+    synchronous calls."""
+    import torch
+    from paper_1704_02357_amd import Batch, Plan
+    from synth import Catalog
+    n, nb = 64, 3300
+    d, r = (Catalog(*(torch.as_tensor(a, device="cuda") for a in (c.pos, c.w, c.nbar)))
+            for c in small_catalogs(2500, 12000, L, seed=7))
+    torch.cuda.synchronize()
+    edges = _edges(n, nb)
+    plan = Plan(n, L, observer=OBS, precision=1, ell_max_hint=4, shape=dict(tile_post=1),
+                stream=torch.cuda.Stream())
+    plan.paint(d, r)
+    ref = plan.compute_multipoles(4, edges)
+    plan.prepare(4, edges, 14500)
+    batch = Batch()
+    batch.add(plan, d, r)
+    print("[case] many bins in a graph", flush=True)
+    for _ in range(3):
+        batch.run(use_graph=True)
+        got = batch.result(0)
+        assert_pole_parity(got, ref, 1, "replay")
+        torch.randn(1 << 20, device="cuda").sum().item()
+    batch.close()
+    plan.close()
